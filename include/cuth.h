@@ -45,6 +45,13 @@
  *    pairs that won; with CUTH_FUSE unset, =1 takes the first triple shape
  *    that fits);
  *    CUTH_FUSE3_SHAPE="R,zc" with CUTH_FUSE=1 and CUTH_FUSE3=1 (default 4,8).
+ *  - CUTH_RESIDENT=0: never run the whole FP32 Chebyshev preconditioner as one
+ *    launch with its vectors on chip (default: single solves of grids of at most
+ *    16 layers whose 64-column tiles of 4, 8 or 16 rows number at most one per
+ *    compute unit, while no other solve of the process does so on the device;
+ *    CUTH_FUSE or CUTH_FUSE3 set, or kernel timing on, asks for sweep launches).
+ *    CUTH_RESIDENT_SPIN=<n>: polls its tiles wait for each other before the
+ *    application is repeated with sweep launches (default 32768).
  *  - CUTH_AUTOTUNE_CACHE=<file>: keep the tuned tile shapes of batches there.
  *  - CUTH_GRAPH=0/1: replay CG chunks from captured HIP graphs, kept by the
  *    handle between solves (default: batches, and single solves of grids of
@@ -52,8 +59,8 @@
  *  - CUTH_REDUCE_ABOVE=<n>: workgroups per problem above which the CG sums go
  *    through a separate reduce launch (default 4096).
  *  - CUTH_LOG=1: tuning results and one line per refinement cycle on stderr.
- * Fused and single sweeps compute the same polynomial in the same order of
- * operations; the choice changes speed, not results beyond FP32 rounding.
+ * On-chip, fused and single sweeps compute the same polynomial;
+ * the choice changes speed, not results beyond FP32 rounding.
  */
 #ifndef CUTH_H
 #define CUTH_H
@@ -353,12 +360,14 @@ cuth_status cuth_precond_apply(cuth_grid g, double dt, int32_t precision, int32_
  * the call allocates nothing.  Every device buffer it needs besides r, z and
  * the operator the handle built at creation (the problem descriptor and its
  * state, the polynomial's constants, the layer coefficients of dt, the
- * reduction partials and the one iterate that is not z) lives in a per-device
- * scratch array of CUTH_NOALLOC_SCRATCH_BYTES; the small parts are written into
- * it by kernel arguments, and the state is cleared on every call.  The sweeps
- * run one per launch (never fused).  Scratch needed: about N * 4 bytes (FP32,
+ * reduction partials, the one iterate that is not z and the on-chip tiles'
+ * exchange) lives in a per-device scratch array of CUTH_NOALLOC_SCRATCH_BYTES;
+ * the small parts are written into it by kernel arguments, and the state is
+ * cleared on every call.  The sweeps run on chip where cuth_precond_apply's do,
+ * else one per launch (never fused).  Scratch needed: about N * 4 bytes (FP32,
  * CUTH_MIXED and CUTH_MIXED16) or N * 8 bytes (CUTH_FP64), plus a few KiB and
- * 384 bytes per stencil workgroup; a grid that needs more returns
+ * 384 bytes per stencil workgroup (and up to 11 MiB on chip, which no grid that
+ * runs there exceeds the array by); a grid that needs more returns
  * CUTH_E_INVALID before any device work, with the sizes in cuth_last_error().
  * All calls on one GPU share its array: calls that overlap in time on one GPU
  * (other host threads, other streams) race and give undefined results.  Returns

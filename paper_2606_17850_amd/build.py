@@ -33,7 +33,7 @@ def build(verbose: bool = False) -> str:
     with tempfile.TemporaryDirectory(prefix="cuth_build_") as tmp:
         objs = []
         jobs = []
-        for src, is_dev in (("kernels.hip", True), ("solver.cpp", False), ("api.cpp", False)):
+        for src, is_dev in (("kernels.hip", True), ("resident.hip", True), ("solver.cpp", False), ("api.cpp", False)):
             obj = os.path.join(tmp, src + ".o")
             cmd = [hipcc] + COMMON + [f"--offload-arch={ARCH}"] + DEVICE_FLAGS
             if is_dev:

@@ -17,6 +17,7 @@ namespace cuth {
 constexpr int kMaxLayers = 64;
 constexpr int kWave = 64;          // CDNA wavefront
 constexpr int kMaxBY = 8;          // rows (wavefronts) per workgroup
+constexpr int kMaxWaves = 16;      // wavefronts of any workgroup
 constexpr int kRedBlocks = 1024;   // workgroups of the 1-D (non-stencil) reduction kernels
 
 // Per-layer coefficients (uniform within a layer).
@@ -126,6 +127,7 @@ struct InnerProb {
     int kcap, pad;
     int f_tile0 = 0, f_ntiles = 0;   // workgroup slots of fused sweep pairs (launch_cheb2_b)
     int t_tile0 = 0, t_ntiles = 0;   // ... of fused sweep triples (launch_cheb3_b)
+    int r_tile0 = 0, r_ntiles = 0, r_ntx = 1;   // tiles of the on-chip preconditioner (launch_cheb_res), r_ntx along x
     // FP64 CG with an FP32 preconditioner (the paper's stage-switched scheme):
     // the update also writes r_lo = (float) r; k_promote_dot reads the
     // preconditioner's z_lo; k_reduce_conv mirrors the stop flag to *done_lo.
@@ -199,6 +201,46 @@ void launch_cheb2_b(const InnerProb<T> *probs, int nprob, int nb, bool pc, bool 
 template <typename T>
 void launch_cheb3_b(const InnerProb<T> *probs, int nprob, int nb, bool pc, bool h16, bool jac, int vx,
                     int R, int zc, int wpr, int j, int zsel, hipStream_t s);
+
+// Tile of the on-chip preconditioner (launch_cheb_res): 64 columns along x and
+// vy * nw rows (nw wavefronts of vy rows each), every layer (nzc: the layer
+// count a lane is built for, >= nz).
+struct ResShape {
+    int nzc = 0, vy = 1, nw = 8;   // nzc 0: not used
+    int rows() const { return vy * nw; }
+};
+constexpr int kResAbort = 6;       // CgState::done of a problem whose tiles waited in vain for a neighbour
+// Device buffers of the on-chip preconditioner's exchange: two sweep parities
+// of `tiles` tiles of edge words, and each tile's tag epoch.  spin: polls a wait
+// may take.
+struct ResArgs {
+    unsigned long long *buf = nullptr;
+    unsigned *epoch = nullptr;
+    int tiles = 0, spin = 0;
+};
+// 64-bit words of one tile's four edges in one parity
+template <typename T>
+inline size_t res_tile_words(int nzc, int vy, int nw) {
+    return 2 * (size_t)(nzc * kWave + vy * nw * nzc) * (sizeof(T) / 4);
+}
+// LDS of a tile: the x-edge corrections and two copies of its rows
+template <typename T>
+inline size_t res_lds(int nzc, int vy, int nw) {
+    return sizeof(T) * ((size_t)2 * vy * nw * nzc + (size_t)2 * nzc * vy * nw * kWave);
+}
+// Clears an exchange of `words` edge words and the `tiles` epochs after them, for
+// its first launch or after one that gave up.
+void launch_res_clear(unsigned long long *buf, size_t words, size_t tiles, hipStream_t s);
+// All sweeps 1 .. k - 1 of the Chebyshev preconditioner in one launch of nb
+// tiles, with every sweep vector on chip: z[zout] = q(A) r and the partials of
+// r^T z (k >= 2).  chk: the convergence test first, as launch_cheb_b.  jac: the
+// Jacobi-scaled sweeps from z_1 in z[0] (zout not 0).  FP16-stored lateral
+// conductances are used where op.hx is set.  False if there is no kernel of
+// this shape.
+template <typename T>
+bool launch_cheb_res(const ResShape &rs, const InnerProb<T> *probs, int nprob, int nb, bool pc, bool jac,
+                     int k, int zout, bool chk, const T *part_in, bool red, T *part_out,
+                     const ResArgs &ra, hipStream_t s);
 
 // Single-pass preconditioner into z[0] (same chk/last behaviour as the sweeps):
 // pm 0: z = r/theta (degree-1 Chebyshev), 1: z = r/diag(A) (Jacobi), 2: z = r,

@@ -64,6 +64,7 @@ struct Shape {
     int vx = 1, by = 1, zc = 8;
     int fr = 0, fzc = 8, fwpr = 1;   // fused pairs: rows per workgroup (0: off), layers, wavefronts per row
     int tr = 0, tzc = 8, twpr = 1;   // fused triples (used only with pairs on)
+    ResShape res;                    // the on-chip preconditioner (before any fusion), nzc 0: off
 };
 
 // Device descriptors, states and reduction partials for up to `cap` problems
@@ -80,6 +81,12 @@ struct Engine {
     float *cheb32 = nullptr, *h_cheb32 = nullptr;
     double *cheb64 = nullptr, *h_cheb64 = nullptr;
     double *part = nullptr, *h_part = nullptr;   // 5 slots of slot_doubles
+    // the on-chip preconditioner's exchange: res_words edge words, then an epoch
+    // per tile; res_ready false: to be cleared before its next use
+    unsigned long long *res_buf = nullptr;
+    size_t res_words = 0, res_tiles = 0;
+    bool res_ready = false;
+    int res_aborts = 0;   // applications that gave up
     hipStream_t own = nullptr;                   // stream for graph capture
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
     // instantiated chunks of CG iterations, by launch configuration: a chunk's

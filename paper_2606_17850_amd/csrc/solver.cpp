@@ -10,6 +10,7 @@
 #include "grid.hpp"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -144,6 +145,81 @@ int graph_env() {
     return e ? (e[0] == '1' ? 1 : 0) : -1;
 }
 constexpr int64_t kGraphMaxN = int64_t(1) << 21;
+// Polls a wait of the on-chip preconditioner may take (a poll takes 0.5 us or
+// more, a wait in earnest one to a few polls).
+constexpr int kResSpin = 1 << 15;
+// (CUTH_RESIDENT_SPIN=<n> sets another bound: the tests of the way back)
+int res_spin() {
+    const char *e = std::getenv("CUTH_RESIDENT_SPIN");
+    const int v = e ? std::atoi(e) : 0;
+    return v > 0 ? v : kResSpin;
+}
+
+// The right to launch on-chip preconditioners on a device.  All tiles of such a
+// launch must run at the same time, so at most one solve of the process uses
+// them per device at a time; another solve meanwhile takes the ordinary
+// launches.  (A solve waits for its stream before it returns, so the lease
+// covers all its launches.)
+class ResLease {
+public:
+    ResLease() = default;
+    ResLease(const ResLease &) = delete;
+    ResLease &operator=(const ResLease &) = delete;
+    ~ResLease() {
+        if (held_) held_->clear(std::memory_order_release);
+    }
+    bool acquire(int device) {
+        static std::atomic_flag busy[kDevices];   // (static: cleared)
+        if (device < 0 || device >= kDevices) return false;
+        if (busy[device].test_and_set(std::memory_order_acquire)) return false;
+        held_ = &busy[device];
+        return true;
+    }
+
+private:
+    static constexpr int kDevices = 64;
+    std::atomic_flag *held_ = nullptr;
+};
+
+// CUTH_RESIDENT=0: never use the on-chip preconditioner.  The settings that
+// force or forbid fused sweeps ask for sweep launches, so they rule it out too.
+bool res_allowed() {
+    const char *e = std::getenv("CUTH_RESIDENT");
+    return !(e && e[0] == '0') && !std::getenv("CUTH_FUSE") && !std::getenv("CUTH_FUSE3");
+}
+
+// Compute units of a device (0 if unknown).
+int device_cus(int device) {
+    int v = 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return 0;
+    return v;
+}
+
+size_t lds_cap();
+
+// Tile of the on-chip preconditioner for an nx x ny x nz grid: the smallest one
+// whose tiles the device's CUs hold at the same time, one per CU (nzc 0: none).
+// The smallest is the fastest or within a few percent of it: 64 x 4, 64 x 8 and
+// 64 x 16 columns take 1.25, 1.24 and 1.51 us per sweep at 64x64x8 and 1.88,
+// 1.70 and 2.08 at 256x256x10, where launches take 3.6 and 4.0 us.
+template <typename T>
+ResShape res_fit(int nx, int ny, int nz, int device) {
+    ResShape none;
+    if (sizeof(T) != 4) return none;
+    const int cus = device_cus(device);
+    const int nzc = nz <= 8 ? 8 : nz <= 12 ? 12 : nz <= 16 ? 16 : 0;
+    if (!nzc) return none;
+    const int tiles[][2] = {{1, 4}, {1, 8}, {2, 8}};
+    for (const auto &c : tiles) {
+        ResShape r;
+        r.nzc = nzc;
+        r.vy = c[0];
+        r.nw = c[1];
+        const int64_t n = (int64_t)tiles_x(nx, 1) * tiles_y(ny, r.rows());
+        if (n <= cus && res_lds<T>(nzc, r.vy, r.nw) + 256 <= lds_cap()) return r;
+    }
+    return none;
+}
 
 // Coefficients of the Chebyshev sweeps for degree k on [lmin, lmax]: with
 // theta = (lmax+lmin)/2, delta = (lmax-lmin)/2, sigma1 = theta/delta,
@@ -175,9 +251,11 @@ ChebConsts make_cheb(double lmin, double lmax, int k) {
     return cc;
 }
 
-// Sweep fusion of a shape: 3 fused triples (and pairs for what is left), 2
-// fused pairs, 0 single sweeps only.
-inline int fuse_level(const Shape &sh) { return sh.tr > 0 && sh.fr > 0 ? 3 : sh.fr > 0 ? 2 : 0; }
+// Sweep fusion of a shape: 4 every sweep in one on-chip launch, 3 fused triples
+// (and pairs for what is left), 2 fused pairs, 0 single sweeps only.
+inline int fuse_level(const Shape &sh) {
+    return sh.res.nzc > 0 ? 4 : sh.tr > 0 && sh.fr > 0 ? 3 : sh.fr > 0 ? 2 : 0;
+}
 
 // The fusion level the preconditioner runs at in precision T (fused launches
 // are FP32 only).
@@ -226,6 +304,8 @@ struct Bytes {
         // z_1 written), then a sweep that reads z_1 and r, then general sweeps
         const bool jac = pm == 3;
         if (jac && k == 1) return scale() + coef;
+        // on chip: r (and z_1 of the scale pass) and the conductances read once, z written
+        if (fuse == 4) return 2.0 * sizeof(T) + coef_sw + (jac ? scale() + coef + sizeof(T) : 0.0);
         double b = jac ? scale() + coef + cheb(2) : cheb(1);
         for (int j = 2; j < k;) {
             const int wd = sweep_width(j, k, fuse);
@@ -410,6 +490,7 @@ void engine_free(Engine &E) {
     host_free(E.h_cheb32);
     host_free(E.h_cheb64);
     host_free(E.h_part);
+    dev_free(E.res_buf);
     if (E.ev_in) (void)hipEventDestroy(E.ev_in);
     if (E.ev_out) (void)hipEventDestroy(E.ev_out);
     if (E.own) (void)hipStreamDestroy(E.own);
@@ -447,7 +528,7 @@ Status upload_cheb(Engine &E, std::vector<Problem *> &ps, hipStream_t s) {
 template <typename T>
 int build_inner(Engine &E, std::vector<Problem *> &ps, const Shape &sh, std::vector<int> &which) {
     InnerProb<T> *h = Sel<T>::h(E);
-    int tile = 0, ftile = 0, ttile = 0, n = 0;
+    int tile = 0, ftile = 0, ttile = 0, rtile = 0, n = 0;
     which.clear();
     for (size_t i = 0; i < ps.size(); ++i) {
         Problem &p = *ps[i];
@@ -473,6 +554,12 @@ int build_inner(Engine &E, std::vector<Problem *> &ps, const Shape &sh, std::vec
         d.z[3] = w.zD;
         d.f_tile0 = d.f_ntiles = 0;
         d.t_tile0 = d.t_ntiles = 0;
+        if (sh.res.nzc > 0) {
+            d.r_tile0 = rtile;
+            d.r_ntx = tiles_x(p.g->nx, 1);
+            d.r_ntiles = d.r_ntx * tiles_y(p.g->ny, sh.res.rows());
+            rtile += d.r_ntiles;
+        }
         if (sh.fr > 0) {
             if (!w.zC || !w.zD) return -1;
             d.f_tile0 = ftile;
@@ -520,7 +607,7 @@ inline void free_pair(int n, int p, int &x, int &y) {
 // a fused pair or triple writes the two other buffers.
 int precond_final(int k, int pm, int fuse) {
     if (k == 1 || pm == 1 || pm == 2) return 0;
-    if (k == 2) return 1;
+    if (k == 2 || fuse == 4) return 1;
     int n = 1, p = 0;   // after mode 1
     for (int j = 2; j < k;) {
         const int wd = sweep_width(j, k, fuse);
@@ -548,6 +635,62 @@ T *red_rr(Engine &E) { return eslot<T>(E, P_RED) + 2 * E.cap; }
 // doubles, past them in either precision)
 double *outer_totals(Engine &E) { return eslot<double>(E, P_RED) + 3 * E.cap; }
 
+// After this many applications that gave up, an engine keeps to sweep launches.
+constexpr int kResAborts = 2;
+// An application gave up: tags and counts are cleared before the next one.
+void res_failed(Engine &E) {
+    ++E.res_aborts;
+    E.res_ready = false;
+    if (log_on()) std::fprintf(stderr, "cuth: on-chip preconditioner gave up waiting; using sweep launches\n");
+}
+
+ResArgs res_args(const Engine &E, int tiles) {
+    ResArgs a;
+    a.buf = E.res_buf;
+    a.epoch = reinterpret_cast<unsigned *>(E.res_buf + E.res_words);
+    a.tiles = tiles;
+    a.spin = res_spin();
+    return a;
+}
+
+// The on-chip shape of a single problem on grid g, where one may be used now (the
+// lease taken); nzc 0 otherwise.
+template <typename T>
+ResShape res_take(const Grid &g, const Shape &sh, int pm, int degree, int aborts, ResLease &lease) {
+    if (sizeof(T) != 4 || !is_cheb(pm) || degree < 2 || !res_allowed() || aborts >= kResAborts) return ResShape{};
+    const ResShape rs = res_fit<T>(g.nx, g.ny, g.nz, g.device);
+    // (one partial sum per tile goes into the sweeps' workgroup slots)
+    if (rs.nzc == 0 || tiles_x(g.nx, 1) * tiles_y(g.ny, rs.rows()) > prob_tiles(g, sh) || !lease.acquire(g.device))
+        return ResShape{};
+    return rs;
+}
+
+// Exchange buffers of the on-chip preconditioner for these problems at shape
+// sh.res, cleared if they are new or if a launch gave up (outside any capture;
+// tag epochs start at 1, above the cleared words' tags of 0).
+template <typename T>
+Status res_prepare(Engine &E, const std::vector<Problem *> &ps, const Shape &sh, hipStream_t s) {
+    size_t tiles = 0;
+    for (const Problem *p : ps) tiles += (size_t)tiles_x(p->g->nx, 1) * tiles_y(p->g->ny, sh.res.rows());
+    const size_t words = 2 * tiles * res_tile_words<T>(sh.res.nzc, sh.res.vy, sh.res.nw);
+    if (words > E.res_words || tiles > E.res_tiles) {
+        // captured chunks hold the old buffer's address
+        for (auto &g : E.graphs) (void)hipGraphExecDestroy(g.second);
+        E.graphs.clear();
+        dev_free(E.res_buf);
+        E.res_words = E.res_tiles = 0;
+        CUTH_TRY(dev_alloc(&E.res_buf, words + (tiles + 1) / 2));
+        E.res_words = words;
+        E.res_tiles = tiles;
+        E.res_ready = false;
+    }
+    if (!E.res_ready) {
+        launch_res_clear(E.res_buf, E.res_words, E.res_tiles, s);
+        E.res_ready = true;
+    }
+    return Status::ok();
+}
+
 // z = q(A) r for every problem of the launch; returns the buffer index of z.
 // chk: the first kernel also runs the convergence test on the update's r^T r.
 template <typename T>
@@ -561,6 +704,16 @@ int enqueue_precond(Engine &E, int nprob, int nb, bool pc, int cs, int pm, const
         launch_scale_b<T>(d, nprob, nb, pc, pm, sh.vx, sh.by, chk, rr_in, red, eslot<T>(E, P_CHEB), s);
         if (red) launch_reduce_b<T>(d, nprob, eslot<T>(E, P_CHEB), red_rz<T>(E), s);
         return 0;
+    }
+    if (sh.res.nzc > 0) {
+        const InnerProb<T> &last = Sel<T>::h(E)[nprob - 1];
+        const int nbr = last.r_tile0 + last.r_ntiles;
+        if (jac) launch_scale_b<T>(d, nprob, nb, pc, pm, sh.vx, sh.by, chk, rr_in, red, eslot<T>(E, P_CHEB), s);
+        if constexpr (sizeof(T) == 4)
+            (void)launch_cheb_res<T>(sh.res, d, nprob, nbr, pc, jac, k, 1, chk && !jac, rr_in, red,
+                                     eslot<T>(E, P_CHEB), res_args(E, nbr), s);
+        if (red) launch_reduce_b<T>(d, nprob, eslot<T>(E, P_CHEB), red_rz<T>(E), s);
+        return 1;
     }
     if (jac) {
         // z_1 = D^{-1} r / theta into z[0] (with the convergence test), then
@@ -683,8 +836,11 @@ int stop_rule(int dev_done, double tn, double dn, double ln, double prev, double
 // drift (||r_true - r_low|| >= 0.5 ||r_true||) and stagnation
 // (||r_true^k|| > 0.9 ||r_true^{k-1}||) tests of Section 4.4.
 template <typename T>
-Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh, int k, int maxit,
+Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, int k, int maxit,
                    int period, bool use_graph, hipStream_t s, Grid *prof) {
+    Shape sh = sh_in;
+    if (sh.res.nzc > 0 && E.res_aborts >= kResAborts) sh.res = ResShape{};
+    if (sh.res.nzc > 0) CUTH_TRY(res_prepare<T>(E, ps, sh, s));
     std::vector<int> which;
     const int nb = build_inner<T>(E, ps, sh, which);
     if (nb < 0) return Status::err(CUTH_E_DEVICE, "internal: inner solve does not fit the engine");
@@ -714,8 +870,8 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh, int k
         p.stop = 0;
     }
     CUTH_HIP(hipMemcpyAsync(Sel<T>::ds(E), hs, sizeof(CgState<T>) * nprob, hipMemcpyHostToDevice, s));
-    const int zfin = enqueue_precond<T>(E, nprob, nb, pc, cs, pm, sh, k, false, red, s, prof);
-    const bool graph = use_graph && period % 2 == 0;
+    int zfin = enqueue_precond<T>(E, nprob, nb, pc, cs, pm, sh, k, false, red, s, prof);
+    bool graph = use_graph && period % 2 == 0;
     // instantiated chunk of `len` iterations (len even: the arguments repeat
     // with the iteration's parity), captured on first use and kept by the
     // engine for later inner solves of the same configuration
@@ -724,7 +880,7 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh, int k
         key << sizeof(T) << ' ' << nprob << ' ' << nb << ' ' << pc << ' ' << cs << ' ' << pm << ' '
             << k << ' ' << len << ' ' << zfin << ' ' << red << ' ' << sh.vx << ',' << sh.by << ','
             << sh.zc << ',' << sh.fr << ',' << sh.fzc << ',' << sh.fwpr << ',' << sh.tr << ','
-            << sh.tzc << ',' << sh.twpr;
+            << sh.tzc << ',' << sh.twpr << ',' << sh.res.nzc << ',' << sh.res.vy << ',' << sh.res.nw;
         for (auto &g : E.graphs)
             if (g.first == key.str()) {
                 out = g.second;
@@ -782,6 +938,20 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh, int k
         CUTH_HIP(hipMemcpyAsync(E.h_part, eslot<T>(E, P_CHK), sizeof(T) * 2 * (size_t)nb,
                                 hipMemcpyDeviceToHost, s));
         CUTH_TRY(sync_stream(s));
+        if (sh.res.nzc > 0 && hs[0].done == kResAbort) {
+            // (a single problem) the tiles of an on-chip application waited in
+            // vain for each other: x and r are those after st.iter iterations,
+            // z is repeated from r with sweep launches and the iteration goes on
+            res_failed(E);
+            sh.res = ResShape{};
+            graph = false;
+            hs[0].done = 0;
+            CUTH_HIP(hipMemcpyAsync(Sel<T>::ds(E), hs, sizeof(CgState<T>), hipMemcpyHostToDevice, s));
+            it = hs[0].iter;
+            --nchecks;
+            zfin = enqueue_precond<T>(E, nprob, nb, pc, cs, pm, sh, k, false, red, s, nullptr);
+            continue;
+        }
         if (prof && prof->prof) {
             // a stop found on the device at CG iteration t (st.iter = t + 1, or
             // t for a breakdown in the direction kernel) empties the sweeps of
@@ -833,7 +1003,7 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh, int k
         p.reason = reason;
         p.drift_stops += reason == 2;
         p.stag_stops += reason == 3;
-        const int fused = fuse_for<T>(sh, p.pm);
+        const int fused = fuse_for<T>(sh_in, p.pm);
         p.bytes += precs_run * by.precond(k, p.pm, fused) * N + iters * (by.dir() + by.update()) * N +
                    nchecks * by.check() * N;
         p.stencils += (int64_t)precs_run * (k - 1) + iters + nchecks;
@@ -1102,8 +1272,11 @@ Status run_refinement(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in,
 // One FP64 inner CG with the FP32 preconditioner on the problems with
 // p->inner set: A x = rhat from x = 0, r = rhat (FP64) and r_lo = (float) r
 // already written.
-Status inner_solve_staged(Engine &E, std::vector<Problem *> &ps, const Shape &sh32,
+Status inner_solve_staged(Engine &E, std::vector<Problem *> &ps, const Shape &sh32_in,
                           const Shape &sh64, int k, int maxit, int period, hipStream_t s) {
+    Shape sh32 = sh32_in;
+    if (sh32.res.nzc > 0 && E.res_aborts >= kResAborts) sh32.res = ResShape{};
+    if (sh32.res.nzc > 0) CUTH_TRY(res_prepare<float>(E, ps, sh32, s));
     std::vector<int> which32, which;
     const int nb32 = build_inner<float>(E, ps, sh32, which32);
     const int nb = build_inner<double>(E, ps, sh64, which);   // p->tile0/ntiles: FP64 tiling
@@ -1117,7 +1290,7 @@ Status inner_solve_staged(Engine &E, std::vector<Problem *> &ps, const Shape &sh
     bool red = false;
     const int above = reduce_above(nprob);
     for (int n = 0; n < nprob; ++n) red = red || ps[which[n]]->ntiles > above;
-    const int zfin32 = precond_final(k, pm, fuse_for<float>(sh32, pm));
+    int zfin32 = precond_final(k, pm, fuse_for<float>(sh32, pm));
     InnerProb<double> *h64 = E.h_in64;
     for (int n = 0; n < nprob; ++n) {
         Problem &p = *ps[which[n]];
@@ -1177,6 +1350,22 @@ Status inner_solve_staged(Engine &E, std::vector<Problem *> &ps, const Shape &sh
         CUTH_HIP(hipMemcpyAsync(E.h_part, eslot<double>(E, P_CHK), sizeof(double) * 2 * (size_t)nb,
                                 hipMemcpyDeviceToHost, s));
         CUTH_TRY(sync_stream(s));
+        if (sh32.res.nzc > 0 && hs[0].done == kResAbort) {
+            // as in inner_solve: z again by sweep launches, then on
+            res_failed(E);
+            sh32.res = ResShape{};
+            zfin32 = precond_final(k, pm, fuse_for<float>(sh32, pm));
+            h64[0].z_lo = zfin32 == 0 ? ps[which[0]]->w32.zA : ps[which[0]]->w32.zB;
+            hs[0].done = 0;
+            hs32[0].done = 0;
+            CUTH_HIP(hipMemcpyAsync(E.in64, h64, sizeof(InnerProb<double>), hipMemcpyHostToDevice, s));
+            CUTH_HIP(hipMemcpyAsync(E.st64, hs, sizeof(CgState<double>), hipMemcpyHostToDevice, s));
+            CUTH_HIP(hipMemcpyAsync(E.st32, hs32, sizeof(CgState<float>), hipMemcpyHostToDevice, s));
+            it = hs[0].iter;
+            --nchecks;
+            precond();
+            continue;
+        }
         bool all_done = true;
         for (int n = 0; n < nprob; ++n) {
             Problem &p = *ps[which[n]];
@@ -1219,7 +1408,7 @@ Status inner_solve_staged(Engine &E, std::vector<Problem *> &ps, const Shape &sh
         p.reason = reason;
         p.drift_stops += reason == 2;
         p.stag_stops += reason == 3;
-        p.bytes += precs_run * (b32.precond(k, p.pm, fuse_for<float>(sh32, p.pm)) + 20.0) * N + iters * (dir64 + b64.update() + 4.0) * N +
+        p.bytes += precs_run * (b32.precond(k, p.pm, fuse_for<float>(sh32_in, p.pm)) + 20.0) * N + iters * (dir64 + b64.update() + 4.0) * N +
                    nchecks * b64.check() * N;
         p.stencils += (int64_t)precs_run * (k - 1) + iters + nchecks;
         p.last_red = p.rr0 > 0 ? std::sqrt(p.true_rr / p.rr0) : 0.0;
@@ -2028,7 +2217,10 @@ Status solve_system(Grid &g, double dt, const double *P, const double *Tn, const
     const int ge = graph_env();
     const bool use_graph = !g.prof && (ge == 1 || (ge < 0 && g.N <= kGraphMaxN));
     Shape sh32 = g.sh32;
-    if (o.precision != CUTH_FP64 && fuse_env() != 0) {
+    ResLease lease;
+    if (o.precision != CUTH_FP64 && !g.prof)
+        sh32.res = res_take<float>(g, sh32, o.preconditioner, o.cheb_degree, g.eng.res_aborts, lease);
+    if (o.precision != CUTH_FP64 && fuse_env() != 0 && sh32.res.nzc == 0) {
         // fused pairs of general sweeps where they are faster on this grid
         CUTH_TRY(alloc_work(g.w32, g.N, true));
         p.w32 = g.w32;
@@ -2609,10 +2801,14 @@ static Status precond_typed(Grid &g, Setup &su, Work<T> &w, const Shape &sh, con
     CgState<T> *hs = Sel<T>::hs(E);
     std::memset(hs, 0, sizeof(CgState<T>));
     CUTH_HIP(hipMemcpyAsync(Sel<T>::ds(E), hs, sizeof(CgState<T>), hipMemcpyHostToDevice, g.stream));
+    if (sh.res.nzc > 0) CUTH_TRY(res_prepare<T>(E, ps, sh, g.stream));
     const int got = enqueue_precond<T>(E, 1, nb, g.per_cell, p.h16 ? CS_F16 : CS_OWN, pm, sh, cc.k,
                                        false, false, g.stream, nullptr);
     if (got != zfin) return Status::err(CUTH_E_DEVICE, "internal: preconditioner buffer mismatch");
     CUTH_HIP(hipGetLastError());
+    // (the caller looks at the stop flag of an on-chip application)
+    if (sh.res.nzc > 0)
+        CUTH_HIP(hipMemcpyAsync(hs, Sel<T>::ds(E), sizeof(CgState<T>), hipMemcpyDeviceToHost, g.stream));
     return sync_stream(g.stream);
 }
 
@@ -2628,6 +2824,13 @@ Status precond_apply(Grid &g, double dt, int precision, int pm, double lmin, dou
         Shape sh32 = g.sh32;
         set_fuse(sh32, g.nx);
         if (sh32.fr > 0) CUTH_TRY(alloc_work(g.w32, g.N, true));
+        ResLease lease;
+        sh32.res = res_take<float>(g, sh32, pm, cc.k, g.eng.res_aborts, lease);
+        st = precond_typed<float>(g, *su, g.w32, sh32, cc, pm, precision == CUTH_MIXED16,
+                                  (const float *)r, (float *)z);
+        if (st.bad() || sh32.res.nzc == 0 || g.eng.h_st32->done != kResAbort) return st;
+        res_failed(g.eng);
+        sh32.res = ResShape{};
         return precond_typed<float>(g, *su, g.w32, sh32, cc, pm, precision == CUTH_MIXED16,
                                     (const float *)r, (float *)z);
     }
@@ -2639,12 +2842,12 @@ Status precond_apply(Grid &g, double dt, int precision, int pm, double lmin, dou
 // Scratch layout of one allocation-free preconditioner application: each part
 // starts on a 256-byte boundary.
 struct NoAllocLayout {
-    size_t desc = 0, state = 0, cheb = 0, layers = 0, part = 0, iter = 0, total = 0;
-    size_t slot_doubles = 0;
+    size_t desc = 0, state = 0, cheb = 0, layers = 0, part = 0, iter = 0, exch = 0, total = 0;
+    size_t slot_doubles = 0, words = 0, tiles = 0;   // words, tiles: the on-chip exchange
 };
 
 template <typename T>
-static NoAllocLayout noalloc_layout(const Grid &g, int kcap, int nb) {
+static NoAllocLayout noalloc_layout(const Grid &g, int kcap, int nb, const ResShape &rs) {
     NoAllocLayout L;
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -2659,25 +2862,39 @@ static NoAllocLayout noalloc_layout(const Grid &g, int kcap, int nb) {
     L.slot_doubles = std::max<size_t>(8 * (size_t)std::max(nb, 1), 3);
     L.part = take(sizeof(double) * L.slot_doubles * P_SLOTS);
     L.iter = take(sizeof(T) * (size_t)g.N);
+    if (rs.nzc > 0) {
+        L.tiles = (size_t)tiles_x(g.nx, 1) * tiles_y(g.ny, rs.rows());
+        L.words = 2 * L.tiles * res_tile_words<T>(rs.nzc, rs.vy, rs.nw);
+        L.exch = take(L.words * sizeof(unsigned long long) + L.tiles * sizeof(unsigned));
+    }
     L.total = off;
     return L;
 }
 
-// z = M^{-1} r as precond_typed runs it with single sweeps, but every buffer
-// the kernels use besides r, z and the grid's planes (the problem descriptor,
-// its state, the sweep constants, the layer coefficients of dt, the partials
-// and the one iterate that is not z) lives in the scratch array; the small ones
-// are written there by kernel arguments.  The state is cleared on every call.
+// z = M^{-1} r as precond_typed runs it on chip (rs) or with single sweeps, but
+// every buffer the kernels use besides r, z and the grid's planes (the problem
+// descriptor, its state, the sweep constants, the layer coefficients of dt, the
+// partials, the one iterate that is not z and the tiles' exchange) lives in the
+// scratch array; the small ones are written there by kernel arguments.  The
+// state and the exchange are cleared on every call.  `aborted`: the on-chip
+// tiles waited in vain and z is to be formed again by sweeps.
 template <typename T>
 static Status precond_noalloc_typed(Grid &g, double dt, const ChebConsts &cc, int pm, bool h16,
-                                    const T *r, T *z) {
+                                    const T *r, T *z, const ResShape &rs, bool &aborted) {
     Shape sh = sizeof(T) == 4 ? g.sh32 : g.sh64;
     sh.fr = 0;
     sh.tr = 0;
+    sh.res = rs;
+    aborted = false;
     const bool h16e = sizeof(T) == 4 && h16 && g.per_cell;
     const int kcap = std::max(cc.k, 1);
     const int nb = prob_tiles(g, sh);
-    const NoAllocLayout L = noalloc_layout<T>(g, kcap, nb);
+    NoAllocLayout L = noalloc_layout<T>(g, kcap, nb, sh.res);
+    if (sh.res.nzc > 0 && L.total > kNoAllocScratchBytes) {
+        // (no on-chip shape of the present tiles needs that much)
+        sh.res = ResShape{};
+        L = noalloc_layout<T>(g, kcap, nb, sh.res);
+    }
     if (L.total > kNoAllocScratchBytes)
         return Status::err(CUTH_E_INVALID,
                            "allocation-free preconditioner: this grid needs " + std::to_string(L.total) +
@@ -2698,7 +2915,7 @@ static Status precond_noalloc_typed(Grid &g, double dt, const ChebConsts &cc, in
         hc[1 + j] = (T)cc.c1[j];
         hc[1 + kcap + j] = (T)cc.c2[j];
     }
-    const int zfin = precond_final(cc.k, pm, 0);
+    const int zfin = precond_final(cc.k, pm, fuse_for<T>(sh, pm));
     T *it = reinterpret_cast<T *>(base + L.iter);
     OpView<T> v{g.nx, g.ny, g.nz, nullptr, nullptr,
                 reinterpret_cast<const LayerCoef<T> *>(base + L.layers), sh.vx, sh.by, sh.zc};
@@ -2731,13 +2948,15 @@ static Status precond_noalloc_typed(Grid &g, double dt, const ChebConsts &cc, in
     d.st = reinterpret_cast<CgState<T> *>(base + L.state);
     d.cheb = reinterpret_cast<const T *>(base + L.cheb);
     d.kcap = kcap;
+    d.r_ntx = tiles_x(g.nx, 1);
+    d.r_ntiles = (int)L.tiles;
     const CgState<T> st0{};
     CUTH_HIP(launch_put(&d, sizeof d, base + L.desc, g.stream));
     CUTH_HIP(launch_put(&st0, sizeof st0, base + L.state, g.stream));
     CUTH_HIP(launch_put(hc.data(), sizeof(T) * hc.size(), base + L.cheb, g.stream));
     CUTH_HIP(launch_put(hl.data(), sizeof(LayerCoef<T>) * hl.size(), base + L.layers, g.stream));
-    // an engine of one problem over the scratch (no host arrays: single sweeps
-    // never read them)
+    // an engine of one problem over the scratch (of the host arrays, the launches
+    // below read the descriptor only)
     Engine E;
     E.cap = 1;
     E.kcap = kcap;
@@ -2745,6 +2964,7 @@ static Status precond_noalloc_typed(Grid &g, double dt, const ChebConsts &cc, in
     E.part = reinterpret_cast<double *>(base + L.part);
     if constexpr (sizeof(T) == 4) {
         E.in32 = reinterpret_cast<InnerProb<float> *>(base + L.desc);
+        E.h_in32 = &d;
         E.st32 = reinterpret_cast<CgState<float> *>(base + L.state);
         E.cheb32 = reinterpret_cast<float *>(base + L.cheb);
     } else {
@@ -2752,20 +2972,42 @@ static Status precond_noalloc_typed(Grid &g, double dt, const ChebConsts &cc, in
         E.st64 = reinterpret_cast<CgState<double> *>(base + L.state);
         E.cheb64 = reinterpret_cast<double *>(base + L.cheb);
     }
+    if (sh.res.nzc > 0) {
+        E.res_buf = reinterpret_cast<unsigned long long *>(base + L.exch);
+        E.res_words = L.words;
+        E.res_tiles = L.tiles;
+        launch_res_clear(E.res_buf, E.res_words, E.res_tiles, g.stream);
+    }
     const int got = enqueue_precond<T>(E, 1, nb, g.per_cell, h16e ? CS_F16 : CS_OWN, pm, sh, cc.k,
                                        false, false, g.stream, nullptr);
     if (got != zfin) return Status::err(CUTH_E_DEVICE, "internal: preconditioner buffer mismatch");
     CUTH_HIP(hipGetLastError());
+    if constexpr (sizeof(T) == 4) {
+        if (sh.res.nzc > 0) {
+            // the stop flag, into the grid's own pinned state
+            CUTH_HIP(hipMemcpyAsync(g.eng.h_st32, E.st32, sizeof(CgState<T>), hipMemcpyDeviceToHost, g.stream));
+            CUTH_TRY(sync_stream(g.stream));
+            aborted = g.eng.h_st32->done == kResAbort;
+            return Status::ok();
+        }
+    }
     return sync_stream(g.stream);
 }
 
 Status precond_apply_noalloc(Grid &g, double dt, int precision, int pm, double lmin, double lmax,
                              int degree, const void *r, void *z) {
     const ChebConsts cc = make_cheb(lmin, lmax, is_cheb(pm) ? degree : 1);
-    if (precision != CUTH_FP64)
-        return precond_noalloc_typed<float>(g, dt, cc, pm, precision == CUTH_MIXED16,
-                                            (const float *)r, (float *)z);
-    return precond_noalloc_typed<double>(g, dt, cc, pm, false, (const double *)r, (double *)z);
+    bool aborted = false;
+    if (precision != CUTH_FP64) {
+        const bool h16 = precision == CUTH_MIXED16;
+        ResLease lease;
+        const ResShape rs = res_take<float>(g, g.sh32, pm, cc.k, g.eng.res_aborts, lease);
+        Status st = precond_noalloc_typed<float>(g, dt, cc, pm, h16, (const float *)r, (float *)z, rs, aborted);
+        if (st.bad() || !aborted) return st;
+        ++g.eng.res_aborts;
+        return precond_noalloc_typed<float>(g, dt, cc, pm, h16, (const float *)r, (float *)z, ResShape{}, aborted);
+    }
+    return precond_noalloc_typed<double>(g, dt, cc, pm, false, (const double *)r, (double *)z, ResShape{}, aborted);
 }
 
 Status adjoint(Grid &g, const double *T, const double *dL_dT, double *dL_dP, double *dL_dk,
