@@ -46,9 +46,11 @@
  *    that fits);
  *    CUTH_FUSE3_SHAPE="R,zc" with CUTH_FUSE=1 and CUTH_FUSE3=1 (default 4,8).
  *  - CUTH_RESIDENT=0: never run the whole FP32 Chebyshev preconditioner as one
- *    launch with its vectors on chip (default: single solves of grids of at most
- *    16 layers whose 64-column tiles of 4, 8 or 16 rows number at most one per
- *    compute unit, while no other solve of the process does so on the device;
+ *    launch with its vectors on chip (default: single solves and mixed batches of
+ *    grids of at most 16 layers, in tiles of 64 columns by 4, 8 or 16 rows of which
+ *    the device holds one per compute unit at a time, in slabs of rows where a
+ *    grid has more of them and the slabs' overlap at most doubles the work, while
+ *    no other solve of the process does so on the device;
  *    CUTH_FUSE or CUTH_FUSE3 set, or kernel timing on, asks for sweep launches).
  *    CUTH_RESIDENT_SPIN=<n>: polls its tiles wait for each other before the
  *    application is repeated with sweep launches (default 32768).
@@ -366,8 +368,9 @@ cuth_status cuth_precond_apply(cuth_grid g, double dt, int32_t precision, int32_
  * cleared on every call.  The sweeps run on chip where cuth_precond_apply's do,
  * else one per launch (never fused).  Scratch needed: about N * 4 bytes (FP32,
  * CUTH_MIXED and CUTH_MIXED16) or N * 8 bytes (CUTH_FP64), plus a few KiB and
- * 384 bytes per stencil workgroup (and up to 11 MiB on chip, which no grid that
- * runs there exceeds the array by); a grid that needs more returns
+ * 384 bytes per stencil workgroup (and up to 42 KiB per on-chip tile; where that
+ * does not fit besides, both calls run the sweeps by launches); a grid that needs
+ * more returns
  * CUTH_E_INVALID before any device work, with the sizes in cuth_last_error().
  * All calls on one GPU share its array: calls that overlap in time on one GPU
  * (other host threads, other streams) race and give undefined results.  Returns

@@ -127,7 +127,7 @@ struct InnerProb {
     int kcap, pad;
     int f_tile0 = 0, f_ntiles = 0;   // workgroup slots of fused sweep pairs (launch_cheb2_b)
     int t_tile0 = 0, t_ntiles = 0;   // ... of fused sweep triples (launch_cheb3_b)
-    int r_tile0 = 0, r_ntiles = 0, r_ntx = 1;   // tiles of the on-chip preconditioner (launch_cheb_res), r_ntx along x
+    int r_ntiles = 0, r_ntx = 1;   // tiles of the on-chip preconditioner (launch_cheb_res), r_ntx along x
     // FP64 CG with an FP32 preconditioner (the paper's stage-switched scheme):
     // the update also writes r_lo = (float) r; k_promote_dot reads the
     // preconditioner's z_lo; k_reduce_conv mirrors the stop flag to *done_lo.
@@ -203,20 +203,36 @@ void launch_cheb3_b(const InnerProb<T> *probs, int nprob, int nb, bool pc, bool 
                     int R, int zc, int wpr, int j, int zsel, hipStream_t s);
 
 // Tile of the on-chip preconditioner (launch_cheb_res): 64 columns along x and
-// vy * nw rows (nw wavefronts of vy rows each), every layer (nzc: the layer
-// count a lane is built for, >= nz).
+// vy * nw rows (nw wavefronts of vy rows each), every layer.  nzc: the layer
+// count a lane is built for (of a single problem; 0: not used).  halo: rows
+// beyond its own that a slab computes (sweeps - 1 of the application).
 struct ResShape {
-    int nzc = 0, vy = 1, nw = 8;   // nzc 0: not used
+    int nzc = 0, vy = 1, nw = 8, halo = 0;
     int rows() const { return vy * nw; }
 };
+// One group of tiles that exchange edges with each other: a problem, or a slab
+// of its rows where the whole has more tiles than the device holds at once.
+// The slab's tiles cover rows from y0 on, nty rows of tiles; it computes halo
+// rows next to its own rows [own0, own1) from r alone, each sweep spoiling one
+// more row from the slab's edge, and writes its own rows.
+struct ResGroup {
+    int tile0, prob;       // first tile of the launch, problem
+    int part0, nty;        // first tile within the problem, rows of tiles
+    int y0, own0, own1;
+    int pad;
+};
 constexpr int kResAbort = 6;       // CgState::done of a problem whose tiles waited in vain for a neighbour
-// Device buffers of the on-chip preconditioner's exchange: two sweep parities
-// of `tiles` tiles of edge words, and each tile's tag epoch.  spin: polls a wait
-// may take.
+// Device buffers of one launch of the on-chip preconditioner: its groups, two
+// sweep parities of `tiles` tiles of edge words, and each tile's tag epoch.
+// width: workgroups of the launch, no fewer than any group has tiles and no more
+// than the device holds at once; each does tiles at this distance in turn.
+// spin: polls a wait may take.
 struct ResArgs {
+    const ResGroup *groups = nullptr;
+    ResGroup one{};   // the only group (ngroups 1: no need to fetch it)
     unsigned long long *buf = nullptr;
     unsigned *epoch = nullptr;
-    int tiles = 0, spin = 0;
+    int ngroups = 0, tiles = 0, width = 0, spin = 0;
 };
 // 64-bit words of one tile's four edges in one parity
 template <typename T>
@@ -228,19 +244,18 @@ template <typename T>
 inline size_t res_lds(int nzc, int vy, int nw) {
     return sizeof(T) * ((size_t)2 * vy * nw * nzc + (size_t)2 * nzc * vy * nw * kWave);
 }
-// Clears an exchange of `words` edge words and the `tiles` epochs after them, for
-// its first launch or after one that gave up.
+// Clears an exchange of `words` edge words and sets the `tiles` epochs after them
+// to 1.
 void launch_res_clear(unsigned long long *buf, size_t words, size_t tiles, hipStream_t s);
-// All sweeps 1 .. k - 1 of the Chebyshev preconditioner in one launch of nb
+// All sweeps 1 .. k - 1 of the Chebyshev preconditioner in one launch over ra.tiles
 // tiles, with every sweep vector on chip: z[zout] = q(A) r and the partials of
 // r^T z (k >= 2).  chk: the convergence test first, as launch_cheb_b.  jac: the
 // Jacobi-scaled sweeps from z_1 in z[0] (zout not 0).  FP16-stored lateral
 // conductances are used where op.hx is set.  False if there is no kernel of
 // this shape.
 template <typename T>
-bool launch_cheb_res(const ResShape &rs, const InnerProb<T> *probs, int nprob, int nb, bool pc, bool jac,
-                     int k, int zout, bool chk, const T *part_in, bool red, T *part_out,
-                     const ResArgs &ra, hipStream_t s);
+bool launch_cheb_res(const ResShape &rs, const InnerProb<T> *probs, bool pc, bool jac, int k, int zout,
+                     bool chk, const T *part_in, bool red, T *part_out, const ResArgs &ra, hipStream_t s);
 
 // Single-pass preconditioner into z[0] (same chk/last behaviour as the sweeps):
 // pm 0: z = r/theta (degree-1 Chebyshev), 1: z = r/diag(A) (Jacobi), 2: z = r,

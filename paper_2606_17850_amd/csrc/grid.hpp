@@ -67,6 +67,19 @@ struct Shape {
     ResShape res;                    // the on-chip preconditioner (before any fusion), nzc 0: off
 };
 
+// Launches of the on-chip preconditioner for a set of problems: one per layer
+// class (8, 12, 16), of `tiles` tiles in groups [g0, g0 + gn) by `width` workgroups,
+// its edge words from word0 and its tiles' epochs from tile0 on.
+struct ResPlan {
+    struct Launch {
+        int nzc, g0, gn, tiles, width;
+        size_t word0, tile0;
+        ResGroup first;
+    };
+    std::vector<Launch> launches;
+    size_t words = 0, tiles = 0, groups = 0;
+};
+
 // Device descriptors, states and reduction partials for up to `cap` problems
 // solved together (a single solve uses a set of one).
 struct Engine {
@@ -81,10 +94,13 @@ struct Engine {
     float *cheb32 = nullptr, *h_cheb32 = nullptr;
     double *cheb64 = nullptr, *h_cheb64 = nullptr;
     double *part = nullptr, *h_part = nullptr;   // 5 slots of slot_doubles
-    // the on-chip preconditioner's exchange: res_words edge words, then an epoch
-    // per tile; res_ready false: to be cleared before its next use
+    // the on-chip preconditioner: edge words, then an epoch per tile; its
+    // groups of tiles; one launch per layer class.  res_ready false: to be cleared
+    // before its next use
     unsigned long long *res_buf = nullptr;
-    size_t res_words = 0, res_tiles = 0;
+    ResGroup *res_groups = nullptr, *h_res_groups = nullptr;
+    size_t res_cap = 0, res_gcap = 0;   // words (epochs included) and groups allocated
+    ResPlan res_plan;
     bool res_ready = false;
     int res_aborts = 0;   // applications that gave up
     hipStream_t own = nullptr;                   // stream for graph capture

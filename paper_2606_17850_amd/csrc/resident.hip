@@ -10,13 +10,23 @@
 // instructions per unknown) and one exchange of the tile's edge values with the
 // four neighbouring tiles (about 1 us through memory, behind the arithmetic
 // where that is long enough).  Per sweep, launches as before -> here: 512x512x16
-// per cell 10.0 -> 3.0 us (256 tiles of 64 x 16 columns: the arithmetic of two
+// per cell 10.0 -> 2.9 us (256 tiles of 64 x 16 columns: the arithmetic of two
 // wavefronts per SIMD, which issue an instruction every 5.5 cycles each),
-// 256x256x10 4.0 -> 1.8 us, 64x64x8 3.6 -> 1.3 us (the exchange).
+// 256x256x10 4.0 -> 1.8 us, 64x64x8 3.6 -> 1.1 us (the exchange).
 //
 // Tiles.  Small tiles shorten the arithmetic, and below 1024 columns per tile
 // the exchange sets the time, so the host takes the smallest of 64 x 4, 64 x 8
 // and 64 x 16 columns whose tiles the CUs hold one each (res_fit).
+//
+// Groups.  Several problems (a batch), or a grid of more tiles than CUs, go
+// through the chip as groups of tiles: a problem is a group, and such a grid is
+// cut into slabs of rows that compute k - 1 rows beyond their own on each side
+// from r alone (a sweep spoils one row more) and write their own.  An
+// application then reads and writes its vectors once whatever the size.  12
+// stacks of 128^2 to 384^2 x 8 to 16 with 4 power maps each: 866 -> 405 ms a
+// solve; one application at 1024x1024x16 (5 slabs, 25 % of the rows computed
+// twice) 1190 -> 540 us with per-layer and 2080 -> 580 us with per-cell
+// conductances, launches as before -> here.
 //
 // Exchange.  Neighbouring tiles may sit on different XCDs, whose L2 caches are
 // not coherent, so edge values go through memory with agent-scope accesses.
@@ -31,13 +41,13 @@
 // lane's registers, and y neighbours of other wavefronts come from an LDS copy
 // of z_j (double-buffered, so one barrier per sweep suffices).
 //
-// Waiting.  Every tile of a problem must be running for its neighbours to make
-// progress.  The host launches at most one workgroup per CU for a single
-// problem and lets one such launch at a time onto a device; every wait is
-// bounded all the same (ResArgs::spin polls): a tile that gives up marks its
-// problem (CgState::done = kResAbort) and ends, its neighbours see the mark and
-// end too, and the host repeats the application with ordinary launches, which
-// only read r.
+// Waiting.  Every tile of a group must be running for its neighbours to make
+// progress.  The host launches at most one workgroup per CU and lets one such
+// launch at a time onto a device; every wait is bounded all the same
+// (ResArgs::spin polls): a tile that gives up marks its problem (CgState::done =
+// kResAbort) and ends, its neighbours see the mark and end too, and the host
+// repeats the application with ordinary launches, which only read r (of several
+// problems: the whole solve of those marked).
 #include "device_util.hpp"
 
 namespace cuth {
@@ -57,6 +67,13 @@ __device__ __forceinline__ u64 get_word(const u64 *q) {
     return __hip_atomic_load((const __attribute__((address_space(1))) u64 *)q, __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
 }
+
+// All loads so far have returned.  Where the compiler cannot see that, it waits at
+// their next possible use, after a branch or at the head of a loop, and with them
+// for every store since (one counter serves both): without these, each sweep
+// waited for the edges just sent to reach memory (512x512x16 3.3 us a sweep
+// instead of 2.9).
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }   // vmcnt 0
 
 // One value as Bits<T>::n consecutive tagged words.
 template <typename T>
@@ -123,10 +140,9 @@ __device__ __forceinline__ T right0(T v) { return dpp_zero<0x130>(v); }
 // tile's edge cells: c2 g (z_neighbour - z).  The first part needs nothing from
 // outside, so the exchange runs behind it.
 template <typename T, bool PC, bool JAC, int NZ, int VY, int NW>
-__global__ __launch_bounds__(kWave *NW, 2) void k_cheb_res(const InnerProb<T> *__restrict__ probs,
-                                                           int nprob, int k, int zout, int chk,
-                                                           const T *__restrict__ part_in, int red,
-                                                           T *__restrict__ part_out, ResArgs ra) {
+__device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs, int k, int zout, int chk,
+                                         const T *__restrict__ part_in, int red, T *__restrict__ part_out,
+                                         const ResArgs &ra, int slot) {
     constexpr int NR = VY * NW;        // rows of a tile
     constexpr int RS = kWave;          // LDS stride of a row's layers (every layer within a paired access's offsets)
     constexpr int WT = Bits<T>::n;
@@ -137,32 +153,40 @@ __global__ __launch_bounds__(kWave *NW, 2) void k_cheb_res(const InnerProb<T> *_
     T *rows = cx + 2 * NR * NZ;
     __shared__ int bad_s;
 
-    const int slot = blockIdx.x;
-    int pidx = 0;
+    int gi = 0;
     {
-        int hi = nprob - 1;
-        while (pidx < hi) {
-            const int mid = (pidx + hi + 1) >> 1;
-            if (probs[mid].r_tile0 <= slot) pidx = mid;
+        int hi = ra.ngroups - 1;
+        while (gi < hi) {
+            const int mid = (gi + hi + 1) >> 1;
+            if (ra.groups[mid].tile0 <= slot) gi = mid;
             else hi = mid - 1;
         }
     }
+    const ResGroup G = ra.ngroups > 1 ? ra.groups[gi] : ra.one;
+    const int pidx = G.prob;
     const InnerProb<T> &P = probs[pidx];
     CgState<T> *st = P.st;
-    const int local = slot - P.r_tile0;
+    const int local = slot - G.tile0, part = G.part0 + local;   // tile of the group, of the problem
     const int done = st->done;
     if (done) return;
-    if (chk && conv_test(st, part_in, red, pidx, P, local == 0)) return;
+    if (chk && conv_test(st, part_in, red, pidx, P, part == 0)) return;
 
-    const int lane = threadIdx.x, w = __builtin_amdgcn_readfirstlane(threadIdx.y);
+    // (opaque: what follows from them is not kept in registers over the loop over
+    // tiles, and the layers' constants come by vector loads, all in flight at once)
+    int lane = threadIdx.x, w = threadIdx.y, zero = 0;
+    asm volatile("" : "+v"(lane), "+v"(w), "+v"(zero));
+    w = __builtin_amdgcn_readfirstlane(w);
     if (tid_lin() == 0) bad_s = 0;
     const OpView<T> &op = P.op;
     const int nx = op.nx, ny = op.ny, nz = op.nz;
     const int64_t plane = (int64_t)nx * ny;
-    const int tx = local % P.r_ntx, ty = local / P.r_ntx;
-    const int nty = P.r_ntiles / P.r_ntx;
-    const bool nbW = tx > 0, nbE = tx + 1 < P.r_ntx, nbS = ty > 0, nbN = ty + 1 < nty;
-    const int i = tx * kWave + lane, row0 = w * VY, j0 = ty * NR + row0;
+    int ntx = P.r_ntx;
+    asm volatile("" : "+s"(ntx));   // (as k below)
+    const int tx = local % ntx, ty = local / ntx;
+    const int nty = G.nty;
+    const bool nbW = tx > 0, nbE = tx + 1 < ntx, nbS = ty > 0, nbN = ty + 1 < nty;
+    const int i = tx * kWave + lane, row0 = w * VY, j0 = G.y0 + ty * NR + row0;
+    const int own0 = G.own0, own1 = G.own1;   // rows this group writes
     const bool act = i < nx;
     // (kernel arguments kept, not read again in every sweep)
     asm volatile("" : "+s"(k));
@@ -185,7 +209,7 @@ __global__ __launch_bounds__(kWave *NW, 2) void k_cheb_res(const InnerProb<T> *_
         return gld(reinterpret_cast<const V *>(b + (size_t)(c * (unsigned)sizeof(V))));
     };
     auto in_grid = [&](int j, int ii) { return j >= 0 && j < ny && ii >= 0 && ii < nx; };
-    auto layer = [&](int l) { return gldc(op.lc + (l < nz ? l : nz - 1)); };
+    auto layer = [&](int l) { return gldc(op.lc + ((l < nz ? l : nz - 1) + zero)); };
     // one lateral conductance from (j, ii) to +x / +y, 0 where there is no such face
     auto lat_at = [&](const T *g, const uint16_t *h, int l, int j, int ii) -> T {
         const T v = h ? (T)h16one(ld(h, l, cell(j, ii))) * layer(l).hs : ld(g, l, cell(j, ii));
@@ -364,12 +388,12 @@ __global__ __launch_bounds__(kWave *NW, 2) void k_cheb_res(const InnerProb<T> *_
         asm volatile("" : "+s"(pb));   // (as row_at)
         // the tile below reads its north side, the tile above its south side
         if (edgeS) {
-            const unsigned q = pb + (unsigned)(slot - P.r_ntx) * kTileBytes + 8u * SY + y_lane;
+            const unsigned q = pb + (unsigned)(slot - ntx) * kTileBytes + 8u * SY + y_lane;
 #pragma unroll
             for (int l = 0; l < NZ; ++l) put_value(word(q) + l * kWave * WT, z[0][l], tag);
         }
         if (edgeN) {
-            const unsigned q = pb + (unsigned)(slot + P.r_ntx) * kTileBytes + y_lane;
+            const unsigned q = pb + (unsigned)(slot + ntx) * kTileBytes + y_lane;
 #pragma unroll
             for (int l = 0; l < NZ; ++l) put_value(word(q) + l * kWave * WT, z[VY - 1][l], tag);
         }
@@ -406,6 +430,7 @@ __global__ __launch_bounds__(kWave *NW, 2) void k_cheb_res(const InnerProb<T> *_
             const int jl = min(j + lane, k - 1);
             vc1 = gld(P.cheb + 1 + jl);
             vc2 = gld(P.cheb + 1 + P.kcap + jl);
+            wait_loads();
         }
         const T c1 = lane_value(vc1, (j - 1) & (kWave - 1)), c2 = lane_value(vc2, (j - 1) & (kWave - 1));
         // The neighbours' edges: a wavefront polls its own x-edge words and, at the
@@ -566,6 +591,7 @@ __global__ __launch_bounds__(kWave *NW, 2) void k_cheb_res(const InnerProb<T> *_
             if (edgeN) y_face(std::integral_constant<int, VY - 1>{});
             if (!edge_y) break;
         }
+        wait_loads();
         if (left <= 0) bad_s = 1;   // (any lane may write it: the value is the same)
         if (wx) {
             // the x-edge cell itself in the LDS copy, and its correction for the lane that holds it
@@ -596,7 +622,7 @@ __global__ __launch_bounds__(kWave *NW, 2) void k_cheb_res(const InnerProb<T> *_
         for (int l = 0; l < NZ; ++l)
 #pragma unroll
             for (int v = 0; v < VY; ++v)
-                if (act && j0 + v < ny && l < nz) {
+                if (act && j0 + v >= own0 && j0 + v < own1 && l < nz) {
                     *as_global(zo + (int64_t)l * plane + (int64_t)(j0 + v) * nx + i) = z[v][l];
                     acc += rr[v][l] * z[v][l];
                 }
@@ -606,9 +632,9 @@ __global__ __launch_bounds__(kWave *NW, 2) void k_cheb_res(const InnerProb<T> *_
         __syncthreads();
         if (bad_s) return false;
         // one partial per tile; the problem's other slots are zero
-        for (int q = local + tid_lin() * P.r_ntiles; q < P.ntiles; q += nthreads() * P.r_ntiles) {
+        for (int q = part + tid_lin() * P.r_ntiles; q < P.ntiles; q += nthreads() * P.r_ntiles) {
             T t = T(0);
-            if (q == local) {
+            if (q == part) {
                 t = sh[0];
                 for (int v = 1; v < NW; ++v) t += sh[v];
             }
@@ -621,6 +647,7 @@ __global__ __launch_bounds__(kWave *NW, 2) void k_cheb_res(const InnerProb<T> *_
 
     put_rows(za, 0);
     if (wx) xe = rows[x_row];
+    wait_loads();
     send(za, 0);
     __syncthreads();
     bool ok = true;
@@ -644,6 +671,26 @@ __global__ __launch_bounds__(kWave *NW, 2) void k_cheb_res(const InnerProb<T> *_
         __hip_atomic_store(&st->done, (int)kResAbort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Tiles blockIdx.x, blockIdx.x + gridDim.x, ... in turn.  All workgroups run at
+// once and a group has no more tiles than there are workgroups, so a workgroup
+// has at most one tile of a group, and by the time it waits in that the groups
+// before are running elsewhere or done: no wait depends on a tile that cannot
+// run.  (A grid of all tiles, handed out as workgroups start, is not enough: a
+// workgroup stays on the XCD it was dispatched to, and one XCD can be full of
+// waiting tiles whose neighbours queue for it while other XCDs idle.)
+template <typename T, bool PC, bool JAC, int NZ, int VY, int NW>
+__global__ __launch_bounds__(kWave *NW, 2) void k_cheb_res(const InnerProb<T> *__restrict__ probs,
+                                                           int k, int zout, int chk,
+                                                           const T *__restrict__ part_in, int red,
+                                                           T *__restrict__ part_out, ResArgs ra) {
+    for (int slot = blockIdx.x;;) {
+        res_tile<T, PC, JAC, NZ, VY, NW>(probs, k, zout, chk, part_in, red, part_out, ra, slot);
+        slot += gridDim.x;
+        if (slot >= ra.tiles) break;
+        __syncthreads();   // the next tile reuses the LDS
+    }
+}
+
 // Cleared edge words (tag 0) and tile epochs of 1.
 __global__ __launch_bounds__(256) void k_res_clear(u64 *buf, size_t words, size_t tiles) {
     const size_t n = (size_t)gridDim.x * blockDim.x, q0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -652,34 +699,38 @@ __global__ __launch_bounds__(256) void k_res_clear(u64 *buf, size_t words, size_
     for (size_t q = q0; q < tiles; q += n) *as_global(epoch + q) = 1u;
 }
 
-template <typename T, bool PC, bool JAC, int NZ, int VY, int NW>
-void launch_one(const InnerProb<T> *probs, int nprob, int nb, int k, int zout, bool chk, const T *part_in,
-                bool red, T *part_out, const ResArgs &ra, hipStream_t s) {
-    hipLaunchKernelGGL((k_cheb_res<T, PC, JAC, NZ, VY, NW>), dim3(nb), dim3(kWave, NW),
-                       res_lds<T>(NZ, VY, NW), s, probs, nprob, k, zout, (int)chk, part_in, (int)red,
-                       part_out, ra);
-}
+// The launch arguments beyond the kernel's shape.
+template <typename T>
+struct Args {
+    const InnerProb<T> *probs;
+    int k, zout, chk;
+    const T *part_in;
+    int red;
+    T *part_out;
+    const ResArgs &ra;
+    hipStream_t s;
+};
 
+template <typename T, bool PC, bool JAC, int NZ, int VY, int NW>
+bool launch_one(const Args<T> &a) {
+    hipLaunchKernelGGL((k_cheb_res<T, PC, JAC, NZ, VY, NW>), dim3(a.ra.width), dim3(kWave, NW),
+                       res_lds<T>(NZ, VY, NW), a.s, a.probs, a.k, a.zout, a.chk, a.part_in, a.red, a.part_out, a.ra);
+    return true;
+}
 template <typename T, bool PC, bool JAC, int VY, int NW>
-bool launch_nz(int nzc, const InnerProb<T> *probs, int nprob, int nb, int k, int zout, bool chk,
-               const T *part_in, bool red, T *part_out, const ResArgs &ra, hipStream_t s) {
+bool launch_nz(int nzc, const Args<T> &a) {
     switch (nzc) {
-    case 8: launch_one<T, PC, JAC, 8, VY, NW>(probs, nprob, nb, k, zout, chk, part_in, red, part_out, ra, s); return true;
-    case 12: launch_one<T, PC, JAC, 12, VY, NW>(probs, nprob, nb, k, zout, chk, part_in, red, part_out, ra, s); return true;
-    case 16: launch_one<T, PC, JAC, 16, VY, NW>(probs, nprob, nb, k, zout, chk, part_in, red, part_out, ra, s); return true;
+    case 8: return launch_one<T, PC, JAC, 8, VY, NW>(a);
+    case 12: return launch_one<T, PC, JAC, 12, VY, NW>(a);
+    case 16: return launch_one<T, PC, JAC, 16, VY, NW>(a);
     }
     return false;
 }
-
 template <typename T, bool PC, bool JAC>
-bool launch_tile(const ResShape &rs, const InnerProb<T> *probs, int nprob, int nb, int k, int zout, bool chk,
-                 const T *part_in, bool red, T *part_out, const ResArgs &ra, hipStream_t s) {
-    if (rs.vy == 2 && rs.nw == 8)
-        return launch_nz<T, PC, JAC, 2, 8>(rs.nzc, probs, nprob, nb, k, zout, chk, part_in, red, part_out, ra, s);
-    if (rs.vy == 1 && rs.nw == 8)
-        return launch_nz<T, PC, JAC, 1, 8>(rs.nzc, probs, nprob, nb, k, zout, chk, part_in, red, part_out, ra, s);
-    if (rs.vy == 1 && rs.nw == 4)
-        return launch_nz<T, PC, JAC, 1, 4>(rs.nzc, probs, nprob, nb, k, zout, chk, part_in, red, part_out, ra, s);
+bool launch_tile(const ResShape &rs, const Args<T> &a) {
+    if (rs.vy == 2 && rs.nw == 8) return launch_nz<T, PC, JAC, 2, 8>(rs.nzc, a);
+    if (rs.vy == 1 && rs.nw == 8) return launch_nz<T, PC, JAC, 1, 8>(rs.nzc, a);
+    if (rs.vy == 1 && rs.nw == 4) return launch_nz<T, PC, JAC, 1, 4>(rs.nzc, a);
     return false;
 }
 
@@ -692,18 +743,14 @@ void launch_res_clear(unsigned long long *buf, size_t words, size_t tiles, hipSt
 }
 
 template <typename T>
-bool launch_cheb_res(const ResShape &rs, const InnerProb<T> *probs, int nprob, int nb, bool pc, bool jac,
-                     int k, int zout, bool chk, const T *part_in, bool red, T *part_out,
-                     const ResArgs &ra, hipStream_t s) {
-    if (pc) {
-        if (jac) return launch_tile<T, true, true>(rs, probs, nprob, nb, k, zout, chk, part_in, red, part_out, ra, s);
-        return launch_tile<T, true, false>(rs, probs, nprob, nb, k, zout, chk, part_in, red, part_out, ra, s);
-    }
-    if (jac) return launch_tile<T, false, true>(rs, probs, nprob, nb, k, zout, chk, part_in, red, part_out, ra, s);
-    return launch_tile<T, false, false>(rs, probs, nprob, nb, k, zout, chk, part_in, red, part_out, ra, s);
+bool launch_cheb_res(const ResShape &rs, const InnerProb<T> *probs, bool pc, bool jac, int k, int zout,
+                     bool chk, const T *part_in, bool red, T *part_out, const ResArgs &ra, hipStream_t s) {
+    const Args<T> a{probs, k, zout, (int)chk, part_in, (int)red, part_out, ra, s};
+    if (pc) return jac ? launch_tile<T, true, true>(rs, a) : launch_tile<T, true, false>(rs, a);
+    return jac ? launch_tile<T, false, true>(rs, a) : launch_tile<T, false, false>(rs, a);
 }
 
-template bool launch_cheb_res<float>(const ResShape &, const InnerProb<float> *, int, int, bool, bool, int,
-                                     int, bool, const float *, bool, float *, const ResArgs &, hipStream_t);
+template bool launch_cheb_res<float>(const ResShape &, const InnerProb<float> *, bool, bool, int, int, bool,
+                                     const float *, bool, float *, const ResArgs &, hipStream_t);
 
 }  // namespace cuth

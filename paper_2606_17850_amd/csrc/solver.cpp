@@ -197,28 +197,91 @@ int device_cus(int device) {
 
 size_t lds_cap();
 
-// Tile of the on-chip preconditioner for an nx x ny x nz grid: the smallest one
-// whose tiles the device's CUs hold at the same time, one per CU (nzc 0: none).
-// The smallest is the fastest or within a few percent of it: 64 x 4, 64 x 8 and
-// 64 x 16 columns take 1.25, 1.24 and 1.51 us per sweep at 64x64x8 and 1.88,
-// 1.70 and 2.08 at 256x256x10, where launches take 3.6 and 4.0 us.
+// The layer count a lane of the on-chip preconditioner is built for (0: none).
+inline int res_class(int nz) { return nz <= 8 ? 8 : nz <= 12 ? 12 : nz <= 16 ? 16 : 0; }
+
+// Rows of an ny-row grid as slabs of at most `nty` rows of tiles each, `halo` rows
+// computed twice at every cut (see ResGroup); empty if a slab cannot hold its
+// halo.  The slabs are as low as their number allows.
+struct ResSlab {
+    int y0, own0, own1, nty;
+};
+std::vector<ResSlab> res_slabs(int ny, int rows, int nty, int halo) {
+    std::vector<ResSlab> out;
+    const int need = tiles_y(ny, rows);
+    if (nty < 1) return out;
+    if (need <= nty) return {ResSlab{0, 0, ny, need}};
+    // own rows of n slabs of c tile rows: the outer two lose one halo, the others two
+    auto covers = [&](int n, int c) { return (int64_t)n * c * rows - 2LL * (n - 1) * halo >= ny && c * rows > 2 * halo; };
+    int n = 2;
+    while (n <= need && !covers(n, nty)) ++n;
+    if (!covers(n, nty)) return out;
+    int c = nty;
+    while (covers(n, c - 1)) --c;
+    for (int q = 0, own = 0; q < n && own < ny; ++q) {
+        ResSlab s;
+        s.own0 = own;
+        s.y0 = q == 0 ? 0 : own - halo;
+        s.own1 = std::min(ny, s.y0 + c * rows - halo);
+        if (s.y0 + c * rows >= ny) s.own1 = ny;
+        s.nty = std::min(c, tiles_y(ny - s.y0, rows));
+        own = s.own1;
+        out.push_back(s);
+    }
+    return out;
+}
+
+// A grid's tiles at shape rs, over all its slabs on a device of `cus` units (0: no fit).
+int64_t res_tiles(int nx, int ny, const ResShape &rs, int cus) {
+    const int ntx = tiles_x(nx, 1);
+    int64_t n = 0;
+    if (ntx <= cus)
+        for (const ResSlab &s : res_slabs(ny, rs.rows(), cus / ntx, rs.halo)) n += (int64_t)ntx * s.nty;
+    return n;
+}
+
+// Tile of the on-chip preconditioner for grids of the given sizes, solved
+// together, at degree k (nzc 0: none).  The smallest tile with which the
+// device's CUs hold all of them at once, one tile each: it is the fastest or
+// within a few percent of it (64 x 4, 64 x 8 and 64 x 16 columns take 1.25, 1.24
+// and 1.51 us per sweep at 64x64x8 and 1.88, 1.70 and 2.08 at 256x256x10, where
+// launches take 3.6 and 4.0 us).  What does not fit at once goes through the
+// device in groups of the largest tile, which does the most work per exchange
+// (2.8 us a sweep for 4.2 M unknowns on all CUs, where launches take 8 to 10),
+// as long as the slabs of a grid compute at most twice its own rows.
+struct ResDims {
+    int nx, ny, nz;
+};
 template <typename T>
-ResShape res_fit(int nx, int ny, int nz, int device) {
+ResShape res_fit(const std::vector<ResDims> &grids, int device, int k) {
     ResShape none;
-    if (sizeof(T) != 4) return none;
+    if (sizeof(T) != 4 || grids.empty()) return none;
     const int cus = device_cus(device);
-    const int nzc = nz <= 8 ? 8 : nz <= 12 ? 12 : nz <= 16 ? 16 : 0;
-    if (!nzc) return none;
-    const int tiles[][2] = {{1, 4}, {1, 8}, {2, 8}};
-    for (const auto &c : tiles) {
-        ResShape r;
-        r.nzc = nzc;
+    int nzc = 0;
+    for (const ResDims &g : grids) {
+        if (!res_class(g.nz)) return none;
+        nzc = std::max(nzc, res_class(g.nz));
+    }
+    const int shapes[][2] = {{1, 4}, {1, 8}, {2, 8}};
+    ResShape r;
+    r.nzc = nzc;
+    r.halo = k - 1;
+    for (const auto &c : shapes) {
         r.vy = c[0];
         r.nw = c[1];
-        const int64_t n = (int64_t)tiles_x(nx, 1) * tiles_y(ny, r.rows());
-        if (n <= cus && res_lds<T>(nzc, r.vy, r.nw) + 256 <= lds_cap()) return r;
+        if (res_lds<T>(nzc, r.vy, r.nw) + 256 > lds_cap()) return none;
+        int64_t n = 0;
+        for (const ResDims &g : grids) n += (int64_t)tiles_x(g.nx, 1) * tiles_y(g.ny, r.rows());
+        if (n <= cus) return r;
     }
-    return none;
+    int64_t total = 0;
+    for (const ResDims &g : grids) {
+        const int64_t n = res_tiles(g.nx, g.ny, r, cus);
+        if (n == 0 || n > 2LL * tiles_x(g.nx, 1) * tiles_y(g.ny, r.rows())) return none;
+        total += n;
+    }
+    // (edge words are addressed by 32-bit byte offsets)
+    return total * 2 * (int64_t)res_tile_words<T>(nzc, r.vy, r.nw) * 8 < (int64_t(1) << 32) ? r : none;
 }
 
 // Coefficients of the Chebyshev sweeps for degree k on [lmin, lmax]: with
@@ -491,6 +554,8 @@ void engine_free(Engine &E) {
     host_free(E.h_cheb64);
     host_free(E.h_part);
     dev_free(E.res_buf);
+    dev_free(E.res_groups);
+    host_free(E.h_res_groups);
     if (E.ev_in) (void)hipEventDestroy(E.ev_in);
     if (E.ev_out) (void)hipEventDestroy(E.ev_out);
     if (E.own) (void)hipStreamDestroy(E.own);
@@ -528,7 +593,7 @@ Status upload_cheb(Engine &E, std::vector<Problem *> &ps, hipStream_t s) {
 template <typename T>
 int build_inner(Engine &E, std::vector<Problem *> &ps, const Shape &sh, std::vector<int> &which) {
     InnerProb<T> *h = Sel<T>::h(E);
-    int tile = 0, ftile = 0, ttile = 0, rtile = 0, n = 0;
+    int tile = 0, ftile = 0, ttile = 0, n = 0;
     which.clear();
     for (size_t i = 0; i < ps.size(); ++i) {
         Problem &p = *ps[i];
@@ -555,10 +620,8 @@ int build_inner(Engine &E, std::vector<Problem *> &ps, const Shape &sh, std::vec
         d.f_tile0 = d.f_ntiles = 0;
         d.t_tile0 = d.t_ntiles = 0;
         if (sh.res.nzc > 0) {
-            d.r_tile0 = rtile;
             d.r_ntx = tiles_x(p.g->nx, 1);
-            d.r_ntiles = d.r_ntx * tiles_y(p.g->ny, sh.res.rows());
-            rtile += d.r_ntiles;
+            d.r_ntiles = (int)res_tiles(p.g->nx, p.g->ny, sh.res, device_cus(p.g->device));
         }
         if (sh.fr > 0) {
             if (!w.zC || !w.zD) return -1;
@@ -644,48 +707,115 @@ void res_failed(Engine &E) {
     if (log_on()) std::fprintf(stderr, "cuth: on-chip preconditioner gave up waiting; using sweep launches\n");
 }
 
-ResArgs res_args(const Engine &E, int tiles) {
+ResArgs res_args(const Engine &E, size_t q) {
+    const ResPlan &p = E.res_plan;
+    const ResPlan::Launch &l = p.launches[q];
+    unsigned *const epochs = reinterpret_cast<unsigned *>(E.res_buf + p.words);
     ResArgs a;
-    a.buf = E.res_buf;
-    a.epoch = reinterpret_cast<unsigned *>(E.res_buf + E.res_words);
-    a.tiles = tiles;
+    a.groups = E.res_groups + l.g0;
+    a.buf = E.res_buf + l.word0;
+    a.epoch = epochs + l.tile0;
+    a.one = l.first;
+    a.ngroups = l.gn;
+    a.tiles = l.tiles;
+    a.width = l.width;
     a.spin = res_spin();
     return a;
 }
 
-// The on-chip shape of a single problem on grid g, where one may be used now (the
-// lease taken); nzc 0 otherwise.
+// The launches and groups of tiles of a set of problems (in their order) at
+// shape rs on a device of `cus` units.
 template <typename T>
-ResShape res_take(const Grid &g, const Shape &sh, int pm, int degree, int aborts, ResLease &lease) {
+ResPlan make_res_plan(const std::vector<ResDims> &grids, const ResShape &rs, int cus, std::vector<ResGroup> &groups) {
+    ResPlan plan;
+    groups.clear();
+    for (int nzc : {8, 12, 16}) {
+        ResPlan::Launch l{nzc, (int)groups.size(), 0, 0, 0, plan.words, plan.tiles, ResGroup{}};
+        for (size_t i = 0; i < grids.size(); ++i) {
+            const ResDims &g = grids[i];
+            if (res_class(g.nz) != nzc) continue;
+            const int ntx = tiles_x(g.nx, 1);
+            int part0 = 0;
+            for (const ResSlab &sl : res_slabs(g.ny, rs.rows(), cus / ntx, rs.halo)) {
+                groups.push_back(ResGroup{l.tiles, (int)i, part0, sl.nty, sl.y0, sl.own0, sl.own1, 0});
+                part0 += ntx * sl.nty;
+                l.tiles += ntx * sl.nty;
+                ++l.gn;
+            }
+        }
+        if (l.tiles == 0) continue;
+        l.width = std::min(l.tiles, cus);
+        l.first = groups[(size_t)l.g0];
+        plan.words += 2 * (size_t)l.tiles * res_tile_words<T>(nzc, rs.vy, rs.nw);
+        plan.tiles += (size_t)l.tiles;
+        plan.launches.push_back(l);
+    }
+    plan.groups = groups.size();
+    return plan;
+}
+// 64-bit words a plan's edge words and epochs take
+inline size_t res_plan_words(const ResPlan &p) { return p.words + (p.tiles + 1) / 2; }
+
+// The on-chip shape for grids solved together on one device, where one may be
+// used now (the lease taken); nzc 0 otherwise.
+template <typename T>
+ResShape res_take(const std::vector<Grid *> &grids, const Shape &sh, int pm, int degree, int aborts, ResLease &lease) {
     if (sizeof(T) != 4 || !is_cheb(pm) || degree < 2 || !res_allowed() || aborts >= kResAborts) return ResShape{};
-    const ResShape rs = res_fit<T>(g.nx, g.ny, g.nz, g.device);
+    std::vector<ResDims> dims;
+    for (const Grid *g : grids) dims.push_back(ResDims{g->nx, g->ny, g->nz});
+    const int device = grids[0]->device;
+    const ResShape rs = res_fit<T>(dims, device, degree);
+    if (rs.nzc == 0) return rs;
     // (one partial sum per tile goes into the sweeps' workgroup slots)
-    if (rs.nzc == 0 || tiles_x(g.nx, 1) * tiles_y(g.ny, rs.rows()) > prob_tiles(g, sh) || !lease.acquire(g.device))
-        return ResShape{};
-    return rs;
+    for (const Grid *g : grids)
+        if (res_tiles(g->nx, g->ny, rs, device_cus(device)) > prob_tiles(*g, sh)) return ResShape{};
+    return lease.acquire(device) ? rs : ResShape{};
 }
 
-// Exchange buffers of the on-chip preconditioner for these problems at shape
-// sh.res, cleared if they are new or if a launch gave up (outside any capture;
-// tag epochs start at 1, above the cleared words' tags of 0).
+// Plan and exchange of the on-chip preconditioner for the problems with p->inner
+// set (in the order of their descriptors) at shape sh.res.  The exchange is
+// cleared if it is new, if a launch gave up, or if tiles may have changed their
+// problem (several groups); outside any capture.
 template <typename T>
 Status res_prepare(Engine &E, const std::vector<Problem *> &ps, const Shape &sh, hipStream_t s) {
-    size_t tiles = 0;
-    for (const Problem *p : ps) tiles += (size_t)tiles_x(p->g->nx, 1) * tiles_y(p->g->ny, sh.res.rows());
-    const size_t words = 2 * tiles * res_tile_words<T>(sh.res.nzc, sh.res.vy, sh.res.nw);
-    if (words > E.res_words || tiles > E.res_tiles) {
-        // captured chunks hold the old buffer's address
+    std::vector<ResDims> dims;
+    int device = 0;
+    for (const Problem *p : ps)
+        if (p->inner) {
+            dims.push_back(ResDims{p->g->nx, p->g->ny, p->g->nz});
+            device = p->g->device;
+        }
+    if (dims.empty()) return Status::ok();
+    std::vector<ResGroup> groups;
+    const ResPlan plan = make_res_plan<T>(dims, sh.res, device_cus(device), groups);
+    const size_t words = res_plan_words(plan);
+    if (words > E.res_cap || plan.groups > E.res_gcap) {
+        CUTH_TRY(sync_stream(s));
+        // captured chunks hold the old buffers' addresses
         for (auto &g : E.graphs) (void)hipGraphExecDestroy(g.second);
         E.graphs.clear();
         dev_free(E.res_buf);
-        E.res_words = E.res_tiles = 0;
-        CUTH_TRY(dev_alloc(&E.res_buf, words + (tiles + 1) / 2));
-        E.res_words = words;
-        E.res_tiles = tiles;
+        dev_free(E.res_groups);
+        host_free(E.h_res_groups);
+        E.res_cap = E.res_gcap = 0;
+        CUTH_TRY(dev_alloc(&E.res_buf, words));
+        CUTH_TRY(dev_alloc(&E.res_groups, plan.groups));
+        CUTH_TRY(host_alloc(&E.h_res_groups, plan.groups));
+        E.res_cap = words;
+        E.res_gcap = plan.groups;
         E.res_ready = false;
     }
-    if (!E.res_ready) {
-        launch_res_clear(E.res_buf, E.res_words, E.res_tiles, s);
+    const bool same = E.res_ready && plan.groups == 1 && E.res_plan.groups == 1 && E.res_plan.tiles == plan.tiles &&
+                      E.res_plan.words == plan.words &&
+                      std::memcmp(E.h_res_groups, groups.data(), sizeof(ResGroup)) == 0;
+    if (!same) {
+        // (the groups' host copy may still be on its way from the solve before:
+        // every inner solve ends with its stream waited for)
+        std::memcpy(E.h_res_groups, groups.data(), sizeof(ResGroup) * plan.groups);
+        CUTH_HIP(hipMemcpyAsync(E.res_groups, E.h_res_groups, sizeof(ResGroup) * plan.groups,
+                                hipMemcpyHostToDevice, s));
+        launch_res_clear(E.res_buf, plan.words, plan.tiles, s);
+        E.res_plan = plan;
         E.res_ready = true;
     }
     return Status::ok();
@@ -706,12 +836,14 @@ int enqueue_precond(Engine &E, int nprob, int nb, bool pc, int cs, int pm, const
         return 0;
     }
     if (sh.res.nzc > 0) {
-        const InnerProb<T> &last = Sel<T>::h(E)[nprob - 1];
-        const int nbr = last.r_tile0 + last.r_ntiles;
         if (jac) launch_scale_b<T>(d, nprob, nb, pc, pm, sh.vx, sh.by, chk, rr_in, red, eslot<T>(E, P_CHEB), s);
         if constexpr (sizeof(T) == 4)
-            (void)launch_cheb_res<T>(sh.res, d, nprob, nbr, pc, jac, k, 1, chk && !jac, rr_in, red,
-                                     eslot<T>(E, P_CHEB), res_args(E, nbr), s);
+            for (size_t q = 0; q < E.res_plan.launches.size(); ++q) {
+                ResShape rs = sh.res;
+                rs.nzc = E.res_plan.launches[q].nzc;
+                (void)launch_cheb_res<T>(rs, d, pc, jac, k, 1, chk && !jac, rr_in, red, eslot<T>(E, P_CHEB),
+                                         res_args(E, q), s);
+            }
         if (red) launch_reduce_b<T>(d, nprob, eslot<T>(E, P_CHEB), red_rz<T>(E), s);
         return 1;
     }
@@ -881,6 +1013,10 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, in
             << k << ' ' << len << ' ' << zfin << ' ' << red << ' ' << sh.vx << ',' << sh.by << ','
             << sh.zc << ',' << sh.fr << ',' << sh.fzc << ',' << sh.fwpr << ',' << sh.tr << ','
             << sh.tzc << ',' << sh.twpr << ',' << sh.res.nzc << ',' << sh.res.vy << ',' << sh.res.nw;
+        if (sh.res.nzc > 0)
+            for (const ResPlan::Launch &l : E.res_plan.launches)
+                key << ' ' << l.nzc << ',' << l.g0 << ',' << l.gn << ',' << l.tiles << ',' << l.word0 << ','
+                    << l.first.prob << ',' << l.first.nty << ',' << l.first.own1;
         for (auto &g : E.graphs)
             if (g.first == key.str()) {
                 out = g.second;
@@ -938,7 +1074,7 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, in
         CUTH_HIP(hipMemcpyAsync(E.h_part, eslot<T>(E, P_CHK), sizeof(T) * 2 * (size_t)nb,
                                 hipMemcpyDeviceToHost, s));
         CUTH_TRY(sync_stream(s));
-        if (sh.res.nzc > 0 && hs[0].done == kResAbort) {
+        if (sh.res.nzc > 0 && nprob == 1 && hs[0].done == kResAbort) {
             // (a single problem) the tiles of an on-chip application waited in
             // vain for each other: x and r are those after st.iter iterations,
             // z is repeated from r with sweep launches and the iteration goes on
@@ -989,11 +1125,22 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, in
     }
     CUTH_TRY(sync_stream(s));
     CUTH_TRY(result);
+    // problems whose on-chip application gave up (several problems are not all at
+    // the same iteration then): solved again from the start with sweep launches
+    std::vector<Problem *> again;
+    for (int n = 0; n < nprob; ++n)
+        if (ps[which[n]]->stop == kResAbort) {
+            again.push_back(ps[which[n]]);
+            const Work<T> &w = Sel<T>::w(*ps[which[n]]);
+            CUTH_HIP(hipMemcpyAsync(w.r, w.rhat, sizeof(T) * (size_t)ps[which[n]]->g->N,
+                                    hipMemcpyDeviceToDevice, s));
+        }
     if (nprob == 1 && p0.stop == 1) p0.su->stop_iter[pi][p0.pm][std::min(p0.cycles, 15)] = hs[0].iter;
     // per-problem results and byte accounting (launches after a problem's stop
     // exit early and move no data)
     for (int n = 0; n < nprob; ++n) {
         Problem &p = *ps[which[n]];
+        if (p.stop == kResAbort) continue;
         const Bytes<T> by(p.g->per_cell, p.h16);
         const double N = (double)p.g->N;
         const int iters = hs[n].iter;
@@ -1016,6 +1163,13 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, in
         } else if (reason == 4) {
             p.status = Status::err(CUTH_E_BREAKDOWN, "CG breakdown (p^T A p <= 0 or non-finite value)");
         }
+    }
+    if (!again.empty()) {
+        res_failed(E);
+        Shape launches = sh_in;
+        launches.res = ResShape{};
+        // (only these have p->inner set still)
+        return inner_solve<T>(E, ps, launches, k, maxit, period, use_graph, s, prof);
     }
     return Status::ok();
 }
@@ -2219,7 +2373,7 @@ Status solve_system(Grid &g, double dt, const double *P, const double *Tn, const
     Shape sh32 = g.sh32;
     ResLease lease;
     if (o.precision != CUTH_FP64 && !g.prof)
-        sh32.res = res_take<float>(g, sh32, o.preconditioner, o.cheb_degree, g.eng.res_aborts, lease);
+        sh32.res = res_take<float>({&g}, sh32, o.preconditioner, o.cheb_degree, g.eng.res_aborts, lease);
     if (o.precision != CUTH_FP64 && fuse_env() != 0 && sh32.res.nzc == 0) {
         // fused pairs of general sweeps where they are faster on this grid
         CUTH_TRY(alloc_work(g.w32, g.N, true));
@@ -2658,7 +2812,13 @@ Status solve_batch(int nsys, Grid *const *grids, int nrhs, const double *const *
                         ? autotune<float>(E, ps, o.cheb_degree, sig.str() + " in", sh_in)
                         : autotune<double>(E, ps, o.cheb_degree, sig.str() + " in", sh_in);
         if (!mixed && !staged) sh64 = sh_in;
-        if (fuse32 && !ts.bad()) {
+        ResLease lease;
+        if (mixed && !ts.bad()) {
+            std::vector<Grid *> gs;
+            for (Problem *p : ps) gs.push_back(p->g);
+            sh_in.res = res_take<float>(gs, sh_in, o.preconditioner, o.cheb_degree, E.res_aborts, lease);
+        }
+        if (fuse32 && !ts.bad() && sh_in.res.nzc == 0) {
             const int kk = is_cheb(o.preconditioner) ? o.cheb_degree : 1;
             for (Problem *p : ps) p->pm = o.preconditioner;
             ts = tune_fuse<float>(E, ps, kk, sh_in, sig.str());
@@ -2812,38 +2972,13 @@ static Status precond_typed(Grid &g, Setup &su, Work<T> &w, const Shape &sh, con
     return sync_stream(g.stream);
 }
 
-Status precond_apply(Grid &g, double dt, int precision, int pm, double lmin, double lmax,
-                     int degree, const void *r, void *z) {
-    Status st;
-    if (degree > g.eng.kcap) return Status::err(CUTH_E_INVALID, "degree above 256");
-    Setup *su = get_setup(g, dt, st);
-    if (!su) return st;
-    // Jacobi and none are single passes; their degree is 1 (the constants are unused)
-    const ChebConsts cc = make_cheb(lmin, lmax, is_cheb(pm) ? degree : 1);
-    if (precision != CUTH_FP64) {
-        Shape sh32 = g.sh32;
-        set_fuse(sh32, g.nx);
-        if (sh32.fr > 0) CUTH_TRY(alloc_work(g.w32, g.N, true));
-        ResLease lease;
-        sh32.res = res_take<float>(g, sh32, pm, cc.k, g.eng.res_aborts, lease);
-        st = precond_typed<float>(g, *su, g.w32, sh32, cc, pm, precision == CUTH_MIXED16,
-                                  (const float *)r, (float *)z);
-        if (st.bad() || sh32.res.nzc == 0 || g.eng.h_st32->done != kResAbort) return st;
-        res_failed(g.eng);
-        sh32.res = ResShape{};
-        return precond_typed<float>(g, *su, g.w32, sh32, cc, pm, precision == CUTH_MIXED16,
-                                    (const float *)r, (float *)z);
-    }
-    CUTH_TRY(alloc_work(g.w64, g.N));
-    return precond_typed<double>(g, *su, g.w64, g.sh64, cc, pm, false, (const double *)r,
-                                 (double *)z);
-}
-
 // Scratch layout of one allocation-free preconditioner application: each part
 // starts on a 256-byte boundary.
 struct NoAllocLayout {
     size_t desc = 0, state = 0, cheb = 0, layers = 0, part = 0, iter = 0, exch = 0, total = 0;
-    size_t slot_doubles = 0, words = 0, tiles = 0;   // words, tiles: the on-chip exchange
+    size_t slot_doubles = 0, groups = 0;
+    ResPlan plan;   // of the on-chip preconditioner
+    std::vector<ResGroup> hg;
 };
 
 template <typename T>
@@ -2863,12 +2998,51 @@ static NoAllocLayout noalloc_layout(const Grid &g, int kcap, int nb, const ResSh
     L.part = take(sizeof(double) * L.slot_doubles * P_SLOTS);
     L.iter = take(sizeof(T) * (size_t)g.N);
     if (rs.nzc > 0) {
-        L.tiles = (size_t)tiles_x(g.nx, 1) * tiles_y(g.ny, rs.rows());
-        L.words = 2 * L.tiles * res_tile_words<T>(rs.nzc, rs.vy, rs.nw);
-        L.exch = take(L.words * sizeof(unsigned long long) + L.tiles * sizeof(unsigned));
+        L.plan = make_res_plan<T>({ResDims{g.nx, g.ny, g.nz}}, rs, device_cus(g.device), L.hg);
+        L.exch = take(res_plan_words(L.plan) * sizeof(unsigned long long));
+        L.groups = take(L.plan.groups * sizeof(ResGroup));
     }
     L.total = off;
     return L;
+}
+
+// The on-chip shape of an application by itself.  Where the allocation-free call
+// can run the grid but has no room for the exchange (a grid of many slabs),
+// neither it nor the ordinary call uses the on-chip path: they return the same
+// bits.
+template <typename T>
+static ResShape precond_res(const Grid &g, const Shape &sh, int kcap, const ResShape &rs) {
+    const int nb = prob_tiles(g, sh);
+    const bool fits = noalloc_layout<T>(g, kcap, nb, rs).total <= kNoAllocScratchBytes,
+               runs = noalloc_layout<T>(g, kcap, nb, ResShape{}).total <= kNoAllocScratchBytes;
+    return fits || !runs ? rs : ResShape{};
+}
+
+Status precond_apply(Grid &g, double dt, int precision, int pm, double lmin, double lmax,
+                     int degree, const void *r, void *z) {
+    Status st;
+    if (degree > g.eng.kcap) return Status::err(CUTH_E_INVALID, "degree above 256");
+    Setup *su = get_setup(g, dt, st);
+    if (!su) return st;
+    // Jacobi and none are single passes; their degree is 1 (the constants are unused)
+    const ChebConsts cc = make_cheb(lmin, lmax, is_cheb(pm) ? degree : 1);
+    if (precision != CUTH_FP64) {
+        Shape sh32 = g.sh32;
+        set_fuse(sh32, g.nx);
+        if (sh32.fr > 0) CUTH_TRY(alloc_work(g.w32, g.N, true));
+        ResLease lease;
+        sh32.res = precond_res<float>(g, g.sh32, std::max(cc.k, 1), res_take<float>({&g}, sh32, pm, cc.k, g.eng.res_aborts, lease));
+        st = precond_typed<float>(g, *su, g.w32, sh32, cc, pm, precision == CUTH_MIXED16,
+                                  (const float *)r, (float *)z);
+        if (st.bad() || sh32.res.nzc == 0 || g.eng.h_st32->done != kResAbort) return st;
+        res_failed(g.eng);
+        sh32.res = ResShape{};
+        return precond_typed<float>(g, *su, g.w32, sh32, cc, pm, precision == CUTH_MIXED16,
+                                    (const float *)r, (float *)z);
+    }
+    CUTH_TRY(alloc_work(g.w64, g.N));
+    return precond_typed<double>(g, *su, g.w64, g.sh64, cc, pm, false, (const double *)r,
+                                 (double *)z);
 }
 
 // z = M^{-1} r as precond_typed runs it on chip (rs) or with single sweeps, but
@@ -2889,17 +3063,14 @@ static Status precond_noalloc_typed(Grid &g, double dt, const ChebConsts &cc, in
     const bool h16e = sizeof(T) == 4 && h16 && g.per_cell;
     const int kcap = std::max(cc.k, 1);
     const int nb = prob_tiles(g, sh);
-    NoAllocLayout L = noalloc_layout<T>(g, kcap, nb, sh.res);
-    if (sh.res.nzc > 0 && L.total > kNoAllocScratchBytes) {
-        // (no on-chip shape of the present tiles needs that much)
-        sh.res = ResShape{};
-        L = noalloc_layout<T>(g, kcap, nb, sh.res);
-    }
+    NoAllocLayout L = noalloc_layout<T>(g, kcap, nb, ResShape{});
     if (L.total > kNoAllocScratchBytes)
         return Status::err(CUTH_E_INVALID,
                            "allocation-free preconditioner: this grid needs " + std::to_string(L.total) +
                                " bytes of scratch, above the " +
                                std::to_string(kNoAllocScratchBytes) + " the library holds per device");
+    sh.res = precond_res<T>(g, sh, kcap, sh.res);
+    if (sh.res.nzc > 0) L = noalloc_layout<T>(g, kcap, nb, sh.res);
     unsigned char *base = nullptr;
     CUTH_HIP(noalloc_scratch(g.device, &base));
     // host images of the small parts
@@ -2949,14 +3120,14 @@ static Status precond_noalloc_typed(Grid &g, double dt, const ChebConsts &cc, in
     d.cheb = reinterpret_cast<const T *>(base + L.cheb);
     d.kcap = kcap;
     d.r_ntx = tiles_x(g.nx, 1);
-    d.r_ntiles = (int)L.tiles;
+    d.r_ntiles = (int)L.plan.tiles;
     const CgState<T> st0{};
     CUTH_HIP(launch_put(&d, sizeof d, base + L.desc, g.stream));
     CUTH_HIP(launch_put(&st0, sizeof st0, base + L.state, g.stream));
     CUTH_HIP(launch_put(hc.data(), sizeof(T) * hc.size(), base + L.cheb, g.stream));
     CUTH_HIP(launch_put(hl.data(), sizeof(LayerCoef<T>) * hl.size(), base + L.layers, g.stream));
-    // an engine of one problem over the scratch (of the host arrays, the launches
-    // below read the descriptor only)
+    // an engine of one problem over the scratch (no host arrays: the launches
+    // below never read them)
     Engine E;
     E.cap = 1;
     E.kcap = kcap;
@@ -2964,7 +3135,6 @@ static Status precond_noalloc_typed(Grid &g, double dt, const ChebConsts &cc, in
     E.part = reinterpret_cast<double *>(base + L.part);
     if constexpr (sizeof(T) == 4) {
         E.in32 = reinterpret_cast<InnerProb<float> *>(base + L.desc);
-        E.h_in32 = &d;
         E.st32 = reinterpret_cast<CgState<float> *>(base + L.state);
         E.cheb32 = reinterpret_cast<float *>(base + L.cheb);
     } else {
@@ -2974,9 +3144,10 @@ static Status precond_noalloc_typed(Grid &g, double dt, const ChebConsts &cc, in
     }
     if (sh.res.nzc > 0) {
         E.res_buf = reinterpret_cast<unsigned long long *>(base + L.exch);
-        E.res_words = L.words;
-        E.res_tiles = L.tiles;
-        launch_res_clear(E.res_buf, E.res_words, E.res_tiles, g.stream);
+        E.res_groups = reinterpret_cast<ResGroup *>(base + L.groups);
+        E.res_plan = L.plan;
+        CUTH_HIP(launch_put(L.hg.data(), sizeof(ResGroup) * L.plan.groups, E.res_groups, g.stream));
+        launch_res_clear(E.res_buf, L.plan.words, L.plan.tiles, g.stream);
     }
     const int got = enqueue_precond<T>(E, 1, nb, g.per_cell, h16e ? CS_F16 : CS_OWN, pm, sh, cc.k,
                                        false, false, g.stream, nullptr);
@@ -3001,7 +3172,7 @@ Status precond_apply_noalloc(Grid &g, double dt, int precision, int pm, double l
     if (precision != CUTH_FP64) {
         const bool h16 = precision == CUTH_MIXED16;
         ResLease lease;
-        const ResShape rs = res_take<float>(g, g.sh32, pm, cc.k, g.eng.res_aborts, lease);
+        const ResShape rs = res_take<float>({&g}, g.sh32, pm, cc.k, g.eng.res_aborts, lease);
         Status st = precond_noalloc_typed<float>(g, dt, cc, pm, h16, (const float *)r, (float *)z, rs, aborted);
         if (st.bad() || !aborted) return st;
         ++g.eng.res_aborts;
