@@ -28,6 +28,11 @@
 // twice) 1190 -> 540 us with per-layer and 2080 -> 580 us with per-cell
 // conductances, launches as before -> here.
 //
+// FP64.  The same kernel with half the rows per tile.  A value takes two exchange
+// words, and the exchange sets the time: 3 us a sweep at 192x128x12, 7 us for a
+// slab of 512x216x16.  One application, launches as before -> here: 64x64x8 238
+// -> 78 us, 192x128x12 250 -> 126; 512x512x16 solves (3 slabs) 175 -> 129 ms.
+//
 // Exchange.  Neighbouring tiles may sit on different XCDs, whose L2 caches are
 // not coherent, so edge values go through memory with agent-scope accesses.
 // Each FP32 word travels in one 64-bit word with a 32-bit tag (launch epoch +
@@ -436,9 +441,10 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
         // The neighbours' edges: a wavefront polls its own x-edge words and, at the
         // tile's y edges, its row's.  First polled before layer IL: what has arrived
         // by then costs no wait.  The largest tile takes the y words LC layers at a
-        // time, for want of registers.
-        constexpr int GL = NZ % 4 == 0 && VY == 1 ? 4 : 2, IL = NZ * 3 / 4 / GL * GL;
-        constexpr int LC = VY == 1 || NZ * (PC ? 4 : 3) * (JAC ? 4 : 3) < 16 * 4 * 3 ? NZ : NZ / 2;
+        // time, for want of registers (all at once spill in FP64 from 12 layers on:
+        // 390x270x14 200 -> 540 us an application).
+        constexpr int GL = sizeof(T) == 4 && NZ % 4 == 0 && VY == 1 ? 4 : 2, IL = NZ * 3 / 4 / GL * GL;
+        constexpr int LC = sizeof(T) == 8 ? (NZ == 8 ? 8 : 4) : VY == 1 || NZ * (PC ? 4 : 3) * (JAC ? 4 : 3) < 16 * 4 * 3 ? NZ : NZ / 2;
         const unsigned tag = epoch + (unsigned)(j - 1);
         unsigned own = (unsigned)((j - 1) & 1) * par_bytes + (unsigned)slot * kTileBytes;
         asm volatile("" : "+s"(own));   // (as row_at)
@@ -728,7 +734,8 @@ bool launch_nz(int nzc, const Args<T> &a) {
 }
 template <typename T, bool PC, bool JAC>
 bool launch_tile(const ResShape &rs, const Args<T> &a) {
-    if (rs.vy == 2 && rs.nw == 8) return launch_nz<T, PC, JAC, 2, 8>(rs.nzc, a);
+    if constexpr (sizeof(T) == 4)
+        if (rs.vy == 2 && rs.nw == 8) return launch_nz<T, PC, JAC, 2, 8>(rs.nzc, a);
     if (rs.vy == 1 && rs.nw == 8) return launch_nz<T, PC, JAC, 1, 8>(rs.nzc, a);
     if (rs.vy == 1 && rs.nw == 4) return launch_nz<T, PC, JAC, 1, 4>(rs.nzc, a);
     return false;
@@ -752,5 +759,7 @@ bool launch_cheb_res(const ResShape &rs, const InnerProb<T> *probs, bool pc, boo
 
 template bool launch_cheb_res<float>(const ResShape &, const InnerProb<float> *, bool, bool, int, int, bool,
                                      const float *, bool, float *, const ResArgs &, hipStream_t);
+template bool launch_cheb_res<double>(const ResShape &, const InnerProb<double> *, bool, bool, int, int, bool,
+                                      const double *, bool, double *, const ResArgs &, hipStream_t);
 
 }  // namespace cuth

@@ -249,26 +249,34 @@ int64_t res_tiles(int nx, int ny, const ResShape &rs, int cus) {
 // device in groups of the largest tile, which does the most work per exchange
 // (2.8 us a sweep for 4.2 M unknowns on all CUs, where launches take 8 to 10),
 // as long as the slabs of a grid compute at most twice its own rows.
+//
+// FP64 tiles hold half the rows, exchange twice the words for each and, with the
+// Jacobi scale in registers, spill: slabs pay only for per-cell conductances
+// without it (1024x1024x16 5.2 -> 3.0 ms an application, 1027x1030x8 2.6 -> 1.5;
+// with per-layer ones 3.3 -> 2.5 and 1.26 -> 1.48, Jacobi-scaled 5.2 -> 5.3).
 struct ResDims {
     int nx, ny, nz;
+    bool cells, jacobi;
 };
 template <typename T>
 ResShape res_fit(const std::vector<ResDims> &grids, int device, int k) {
     ResShape none;
-    if (sizeof(T) != 4 || grids.empty()) return none;
+    if (grids.empty()) return none;
     const int cus = device_cus(device);
     int nzc = 0;
     for (const ResDims &g : grids) {
         if (!res_class(g.nz)) return none;
         nzc = std::max(nzc, res_class(g.nz));
     }
-    const int shapes[][2] = {{1, 4}, {1, 8}, {2, 8}};
+    const std::vector<std::pair<int, int>> shapes =
+        sizeof(T) == 4 ? std::vector<std::pair<int, int>>{{1, 4}, {1, 8}, {2, 8}}
+                       : std::vector<std::pair<int, int>>{{1, 4}, {1, 8}};
     ResShape r;
     r.nzc = nzc;
     r.halo = k - 1;
     for (const auto &c : shapes) {
-        r.vy = c[0];
-        r.nw = c[1];
+        r.vy = c.first;
+        r.nw = c.second;
         if (res_lds<T>(nzc, r.vy, r.nw) + 256 > lds_cap()) return none;
         int64_t n = 0;
         for (const ResDims &g : grids) n += (int64_t)tiles_x(g.nx, 1) * tiles_y(g.ny, r.rows());
@@ -277,7 +285,10 @@ ResShape res_fit(const std::vector<ResDims> &grids, int device, int k) {
     int64_t total = 0;
     for (const ResDims &g : grids) {
         const int64_t n = res_tiles(g.nx, g.ny, r, cus);
-        if (n == 0 || n > 2LL * tiles_x(g.nx, 1) * tiles_y(g.ny, r.rows())) return none;
+        const int64_t own = (int64_t)tiles_x(g.nx, 1) * tiles_y(g.ny, r.rows());
+        if (n == 0 || n > 2 * own) return none;
+        if (sizeof(T) == 8 && own > cus && (!g.cells || g.jacobi || n * kWave * r.rows() > 2LL * g.nx * g.ny))
+            return none;
         total += n;
     }
     // (edge words are addressed by 32-bit byte offsets)
@@ -325,7 +336,7 @@ inline int fuse_level(const Shape &sh) {
 template <typename T>
 int fuse_for(const Shape &sh, int pm) {
     (void)pm;
-    return sizeof(T) == 4 ? fuse_level(sh) : 0;
+    return sizeof(T) == 4 || sh.res.nzc > 0 ? fuse_level(sh) : 0;
 }
 
 // Number of sweeps the launch at sweep j of a degree-k preconditioner covers
@@ -760,9 +771,9 @@ inline size_t res_plan_words(const ResPlan &p) { return p.words + (p.tiles + 1) 
 // used now (the lease taken); nzc 0 otherwise.
 template <typename T>
 ResShape res_take(const std::vector<Grid *> &grids, const Shape &sh, int pm, int degree, int aborts, ResLease &lease) {
-    if (sizeof(T) != 4 || !is_cheb(pm) || degree < 2 || !res_allowed() || aborts >= kResAborts) return ResShape{};
+    if (!is_cheb(pm) || degree < 2 || !res_allowed() || aborts >= kResAborts) return ResShape{};
     std::vector<ResDims> dims;
-    for (const Grid *g : grids) dims.push_back(ResDims{g->nx, g->ny, g->nz});
+    for (const Grid *g : grids) dims.push_back(ResDims{g->nx, g->ny, g->nz, g->per_cell, pm == CUTH_PC_CHEBYSHEV_JACOBI});
     const int device = grids[0]->device;
     const ResShape rs = res_fit<T>(dims, device, degree);
     if (rs.nzc == 0) return rs;
@@ -782,7 +793,7 @@ Status res_prepare(Engine &E, const std::vector<Problem *> &ps, const Shape &sh,
     int device = 0;
     for (const Problem *p : ps)
         if (p->inner) {
-            dims.push_back(ResDims{p->g->nx, p->g->ny, p->g->nz});
+            dims.push_back(ResDims{p->g->nx, p->g->ny, p->g->nz, p->g->per_cell, p->pm == CUTH_PC_CHEBYSHEV_JACOBI});
             device = p->g->device;
         }
     if (dims.empty()) return Status::ok();
@@ -837,13 +848,12 @@ int enqueue_precond(Engine &E, int nprob, int nb, bool pc, int cs, int pm, const
     }
     if (sh.res.nzc > 0) {
         if (jac) launch_scale_b<T>(d, nprob, nb, pc, pm, sh.vx, sh.by, chk, rr_in, red, eslot<T>(E, P_CHEB), s);
-        if constexpr (sizeof(T) == 4)
-            for (size_t q = 0; q < E.res_plan.launches.size(); ++q) {
-                ResShape rs = sh.res;
-                rs.nzc = E.res_plan.launches[q].nzc;
-                (void)launch_cheb_res<T>(rs, d, pc, jac, k, 1, chk && !jac, rr_in, red, eslot<T>(E, P_CHEB),
-                                         res_args(E, q), s);
-            }
+        for (size_t q = 0; q < E.res_plan.launches.size(); ++q) {
+            ResShape rs = sh.res;
+            rs.nzc = E.res_plan.launches[q].nzc;
+            (void)launch_cheb_res<T>(rs, d, pc, jac, k, 1, chk && !jac, rr_in, red, eslot<T>(E, P_CHEB),
+                                     res_args(E, q), s);
+        }
         if (red) launch_reduce_b<T>(d, nprob, eslot<T>(E, P_CHEB), red_rz<T>(E), s);
         return 1;
     }
@@ -2385,8 +2395,10 @@ Status solve_system(Grid &g, double dt, const double *P, const double *Tn, const
         const int kk = is_cheb(o.preconditioner) ? o.cheb_degree : 1;
         CUTH_TRY(tune_fuse<float>(g.eng, ps, kk, sh32, sig.str()));
     }
-    Status rs = run_set(g.eng, ps, g.stream, sh32, g.sh64, o, period, use_graph, &g,
-                        p.csr ? &sh_csr : nullptr);
+    Shape sh64 = p.csr ? sh_csr : g.sh64;
+    if (o.precision == CUTH_FP64 && !p.csr && !g.prof)
+        sh64.res = res_take<double>({&g}, sh64, o.preconditioner, o.cheb_degree, g.eng.res_aborts, lease);
+    Status rs = run_set(g.eng, ps, g.stream, sh32, g.sh64, o, period, use_graph, &g, &sh64);
     if (rs.code == CUTH_E_DEVICE || rs.code == CUTH_E_NOMEM) return rs;
     CUTH_HIP(hipEventRecord(g.ev2, g.stream));
     CUTH_TRY(sync_stream(g.stream));
@@ -2813,10 +2825,11 @@ Status solve_batch(int nsys, Grid *const *grids, int nrhs, const double *const *
                         : autotune<double>(E, ps, o.cheb_degree, sig.str() + " in", sh_in);
         if (!mixed && !staged) sh64 = sh_in;
         ResLease lease;
-        if (mixed && !ts.bad()) {
+        if (!staged && !ts.bad()) {
             std::vector<Grid *> gs;
             for (Problem *p : ps) gs.push_back(p->g);
-            sh_in.res = res_take<float>(gs, sh_in, o.preconditioner, o.cheb_degree, E.res_aborts, lease);
+            sh_in.res = mixed ? res_take<float>(gs, sh_in, o.preconditioner, o.cheb_degree, E.res_aborts, lease)
+                              : res_take<double>(gs, sh_in, o.preconditioner, o.cheb_degree, E.res_aborts, lease);
         }
         if (fuse32 && !ts.bad() && sh_in.res.nzc == 0) {
             const int kk = is_cheb(o.preconditioner) ? o.cheb_degree : 1;
@@ -2826,7 +2839,7 @@ Status solve_batch(int nsys, Grid *const *grids, int nrhs, const double *const *
         if (!ts.bad()) {
             const int period = o.check_period > 0 ? o.check_period : 20;
             const bool use_graph = graph_env() != 0;
-            ts = run_set(E, ps, user, sh_in, sh64, o, period, use_graph, nullptr);
+            ts = run_set(E, ps, user, sh_in, sh64, o, period, use_graph, nullptr, &sh_in);
         }
         if (ts.code == CUTH_E_DEVICE || ts.code == CUTH_E_NOMEM) batch_pool_free(bp);
         if (ts.code == CUTH_E_DEVICE || ts.code == CUTH_E_NOMEM || ts.code == CUTH_E_INVALID) return ts;
@@ -2998,7 +3011,7 @@ static NoAllocLayout noalloc_layout(const Grid &g, int kcap, int nb, const ResSh
     L.part = take(sizeof(double) * L.slot_doubles * P_SLOTS);
     L.iter = take(sizeof(T) * (size_t)g.N);
     if (rs.nzc > 0) {
-        L.plan = make_res_plan<T>({ResDims{g.nx, g.ny, g.nz}}, rs, device_cus(g.device), L.hg);
+        L.plan = make_res_plan<T>({ResDims{g.nx, g.ny, g.nz, g.per_cell, false}}, rs, device_cus(g.device), L.hg);
         L.exch = take(res_plan_words(L.plan) * sizeof(unsigned long long));
         L.groups = take(L.plan.groups * sizeof(ResGroup));
     }
@@ -3041,8 +3054,13 @@ Status precond_apply(Grid &g, double dt, int precision, int pm, double lmin, dou
                                     (const float *)r, (float *)z);
     }
     CUTH_TRY(alloc_work(g.w64, g.N));
-    return precond_typed<double>(g, *su, g.w64, g.sh64, cc, pm, false, (const double *)r,
-                                 (double *)z);
+    Shape sh64 = g.sh64;
+    ResLease lease;
+    sh64.res = precond_res<double>(g, g.sh64, std::max(cc.k, 1), res_take<double>({&g}, sh64, pm, cc.k, g.eng.res_aborts, lease));
+    st = precond_typed<double>(g, *su, g.w64, sh64, cc, pm, false, (const double *)r, (double *)z);
+    if (st.bad() || sh64.res.nzc == 0 || g.eng.h_st64->done != kResAbort) return st;
+    res_failed(g.eng);
+    return precond_typed<double>(g, *su, g.w64, g.sh64, cc, pm, false, (const double *)r, (double *)z);
 }
 
 // z = M^{-1} r as precond_typed runs it on chip (rs) or with single sweeps, but
@@ -3153,14 +3171,13 @@ static Status precond_noalloc_typed(Grid &g, double dt, const ChebConsts &cc, in
                                        false, false, g.stream, nullptr);
     if (got != zfin) return Status::err(CUTH_E_DEVICE, "internal: preconditioner buffer mismatch");
     CUTH_HIP(hipGetLastError());
-    if constexpr (sizeof(T) == 4) {
-        if (sh.res.nzc > 0) {
-            // the stop flag, into the grid's own pinned state
-            CUTH_HIP(hipMemcpyAsync(g.eng.h_st32, E.st32, sizeof(CgState<T>), hipMemcpyDeviceToHost, g.stream));
-            CUTH_TRY(sync_stream(g.stream));
-            aborted = g.eng.h_st32->done == kResAbort;
-            return Status::ok();
-        }
+    if (sh.res.nzc > 0) {
+        // the stop flag, into the grid's own pinned state
+        CgState<T> *const hs = Sel<T>::hs(g.eng);
+        CUTH_HIP(hipMemcpyAsync(hs, Sel<T>::ds(E), sizeof(CgState<T>), hipMemcpyDeviceToHost, g.stream));
+        CUTH_TRY(sync_stream(g.stream));
+        aborted = hs->done == kResAbort;
+        return Status::ok();
     }
     return sync_stream(g.stream);
 }
@@ -3178,6 +3195,11 @@ Status precond_apply_noalloc(Grid &g, double dt, int precision, int pm, double l
         ++g.eng.res_aborts;
         return precond_noalloc_typed<float>(g, dt, cc, pm, h16, (const float *)r, (float *)z, ResShape{}, aborted);
     }
+    ResLease lease;
+    const ResShape rs = res_take<double>({&g}, g.sh64, pm, cc.k, g.eng.res_aborts, lease);
+    const Status st = precond_noalloc_typed<double>(g, dt, cc, pm, false, (const double *)r, (double *)z, rs, aborted);
+    if (st.bad() || !aborted) return st;
+    ++g.eng.res_aborts;
     return precond_noalloc_typed<double>(g, dt, cc, pm, false, (const double *)r, (double *)z, ResShape{}, aborted);
 }
 
