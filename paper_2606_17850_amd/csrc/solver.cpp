@@ -357,9 +357,11 @@ template <typename T>
 struct Bytes {
     double coef;     // per-cell lateral conductances read by one CG stencil pass
     double coef_sw;  // ... by one Chebyshev sweep (FP16-stored: 2 x 2 B)
+    bool z1_pass;    // Jacobi-scaled, on chip: z_1 by a pass of its own
     explicit Bytes(bool per_cell, bool h16 = false)
         : coef(per_cell ? 2.0 * sizeof(T) : 0.0),
-          coef_sw(per_cell ? (h16 ? 4.0 : 2.0 * sizeof(T)) : 0.0) {}
+          coef_sw(per_cell ? (h16 ? 4.0 : 2.0 * sizeof(T)) : 0.0),
+          z1_pass(per_cell && h16) {}
     double cheb(int mode) const { return (mode == 1 ? 2 : mode == 2 ? 3 : 4) * sizeof(T) + coef_sw; }
     double dir() const { return 4.0 * sizeof(T) + coef; }
     double update() const { return 6.0 * sizeof(T); }
@@ -378,8 +380,8 @@ struct Bytes {
         // z_1 written), then a sweep that reads z_1 and r, then general sweeps
         const bool jac = pm == 3;
         if (jac && k == 1) return scale() + coef;
-        // on chip: r (and z_1 of the scale pass) and the conductances read once, z written
-        if (fuse == 4) return 2.0 * sizeof(T) + coef_sw + (jac ? scale() + coef + sizeof(T) : 0.0);
+        // on chip: r (and z_1 of a scale pass) and the conductances read once, z written
+        if (fuse == 4) return 2.0 * sizeof(T) + coef_sw + (jac && z1_pass ? scale() + coef + sizeof(T) : 0.0);
         double b = jac ? scale() + coef + cheb(2) : cheb(1);
         for (int j = 2; j < k;) {
             const int wd = sweep_width(j, k, fuse);
@@ -847,11 +849,12 @@ int enqueue_precond(Engine &E, int nprob, int nb, bool pc, int cs, int pm, const
         return 0;
     }
     if (sh.res.nzc > 0) {
-        if (jac) launch_scale_b<T>(d, nprob, nb, pc, pm, sh.vx, sh.by, chk, rr_in, red, eslot<T>(E, P_CHEB), s);
+        const bool z1 = jac && cs == CS_F16;   // (see k_cheb_res)
+        if (z1) launch_scale_b<T>(d, nprob, nb, pc, pm, sh.vx, sh.by, chk, rr_in, red, eslot<T>(E, P_CHEB), s);
         for (size_t q = 0; q < E.res_plan.launches.size(); ++q) {
             ResShape rs = sh.res;
             rs.nzc = E.res_plan.launches[q].nzc;
-            (void)launch_cheb_res<T>(rs, d, pc, jac, k, 1, chk && !jac, rr_in, red, eslot<T>(E, P_CHEB),
+            (void)launch_cheb_res<T>(rs, d, pc, jac, k, 1, chk && !z1, rr_in, red, eslot<T>(E, P_CHEB),
                                      res_args(E, q), s);
         }
         if (red) launch_reduce_b<T>(d, nprob, eslot<T>(E, P_CHEB), red_rz<T>(E), s);
