@@ -785,6 +785,31 @@ ResShape res_take(const std::vector<Grid *> &grids, const Shape &sh, int pm, int
     return lease.acquire(device) ? rs : ResShape{};
 }
 
+// Tiles of the CG kernels for a grid whose preconditioner is on chip (a shape set
+// in the environment stays).  A lane's march over 8 layers is one chain of loads:
+// where that leaves less than a wavefront per SIMD, the chain's latency is the
+// time, and 2 layers a lane and 4 rows a workgroup (as many partial sums as
+// before) halve it: mixed 64x64x8 3.45 -> 3.10 ms, 256x256x10 11.3 -> 10.3 (390x270x14,
+// two wavefronts per SIMD, loses 4 %).  FP64 vectors take 4 rows a workgroup in
+// any case: every workgroup sums all partials, and 512x512x16 has 4096 of them
+// otherwise (stage-switched solve 42.1 -> 39.8 ms).
+template <typename T>
+Shape cg_shape(const Grid &g, const Shape &def, const Engine &E) {
+    if (std::getenv(sizeof(T) == 4 ? "CUTH_SHAPE32" : "CUTH_SHAPE64")) return def;
+    Shape s = def;
+    if ((int64_t)prob_tiles(g, def) * def.by < 4LL * device_cus(g.device)) {
+        s.by = 4;
+        s.zc = 2;
+    } else if (sizeof(T) == 8) {
+        s.by = 4;
+    }
+    // (as in build_inner: two partials per workgroup; one per on-chip tile)
+    const int64_t n = prob_tiles(g, s);
+    const bool fits = (size_t)n * 2 <= E.slot_doubles &&
+                      (s.res.nzc == 0 || res_tiles(g.nx, g.ny, s.res, device_cus(g.device)) <= n);
+    return fits ? s : def;
+}
+
 // Plan and exchange of the on-chip preconditioner for the problems with p->inner
 // set (in the order of their descriptors) at shape sh.res.  The exchange is
 // cleared if it is new, if a launch gave up, or if tiles may have changed their
@@ -2401,7 +2426,13 @@ Status solve_system(Grid &g, double dt, const double *P, const double *Tn, const
     Shape sh64 = p.csr ? sh_csr : g.sh64;
     if (o.precision == CUTH_FP64 && !p.csr && !g.prof)
         sh64.res = res_take<double>({&g}, sh64, o.preconditioner, o.cheb_degree, g.eng.res_aborts, lease);
-    Status rs = run_set(g.eng, ps, g.stream, sh32, g.sh64, o, period, use_graph, &g, &sh64);
+    Shape outer64 = g.sh64;
+    if (sh64.res.nzc > 0) sh64 = cg_shape<double>(g, sh64, g.eng);
+    if (sh32.res.nzc > 0) {
+        if (o.precision == CUTH_ADAPTIVE) outer64 = cg_shape<double>(g, outer64, g.eng);
+        else sh32 = cg_shape<float>(g, sh32, g.eng);
+    }
+    Status rs = run_set(g.eng, ps, g.stream, sh32, outer64, o, period, use_graph, &g, &sh64);
     if (rs.code == CUTH_E_DEVICE || rs.code == CUTH_E_NOMEM) return rs;
     CUTH_HIP(hipEventRecord(g.ev2, g.stream));
     CUTH_TRY(sync_stream(g.stream));
