@@ -28,6 +28,11 @@
 // twice) 1190 -> 540 us with per-layer and 2080 -> 580 us with per-cell
 // conductances, launches as before -> here.
 //
+// 17 to 20 layers (FP32) take 14 rows, which fill the LDS, where the plain
+// per-layer kernel fits its registers (255), else 8: 1024x1024x20, 6 slabs, 1190 ->
+// 620 us an application, a backward-Euler step 9.4 -> 6.0 ms (14 slabs of 8-row
+// tiles: 1070 us).
+//
 // FP64.  The same kernel with half the rows per tile.  A value takes two exchange
 // words, and the exchange sets the time: 3 us a sweep at 192x128x12, 7 us for a
 // slab of 512x216x16.  One application, launches as before -> here: 64x64x8 238
@@ -332,24 +337,33 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
         for (int v = 0; v < (PC ? VY : 1); ++v) gxp[v][l] = lane == kWave - 1 ? T(0) : gxp[v][l];
     // the lane's x-edge cell: side, row and layer, conductance of its face to the
     // neighbouring tile, value in the current iterate
-    constexpr int XI = 2 * VY * NZ;   // x-edge cells of a wavefront: at most one per lane
-    static_assert(XI <= kWave, "one x-edge cell per lane");
-    const int xq = lane < XI ? lane : 0;
-    const int xs = xq & 1, xr = (xq >> 1) / NZ, xl = (xq >> 1) % NZ;   // (sides alternate: two LDS banks at a time)
-    const bool wx = lane < XI && (xs == 0 ? nbW : nbE);
-    const int xi = tx * kWave + (xs == 0 ? 0 : kWave - 1);   // its column
-    const T ge = wx ? gx_at(xl, j0 + xr, xs == 0 ? xi - 1 : xi) : T(0);
-    [[maybe_unused]] T de = T(1);
-    if constexpr (JAC) {
-        const LayerCoef<T> L = layer(xl);
-        const int j = j0 + xr;
-        const T d = L.sink + gx_at(xl, j, xi - 1) + gx_at(xl, j, xi) + gy_at(xl, j - 1, xi) + gy_at(xl, j, xi) +
-                    L.gzd + L.gzu;
-        de = wx && in_grid(j, xi) && xl < nz ? recip(d) : T(0);
+    constexpr int XI = 2 * VY * NZ;   // x-edge cells of a wavefront: XN or fewer per lane
+    constexpr int XN = (XI + kWave - 1) / kWave;
+    const int xs = lane & 1;                                     // (sides alternate: two LDS banks at a time)
+    const int xi = tx * kWave + (xs == 0 ? 0 : kWave - 1);       // its column
+    bool wx[XN];
+    T ge[XN], xe[XN];
+    [[maybe_unused]] T de[XN];
+    int x_at[XN], x_row[XN];   // its slot in cx and in LDS copy 0
+    unsigned side_at[XN];
+#pragma unroll
+    for (int n = 0; n < XN; ++n) {
+        const int xq = lane + n * kWave < XI ? lane + n * kWave : xs;
+        const int xr = (xq >> 1) / NZ, xl = (xq >> 1) % NZ;
+        wx[n] = lane + n * kWave < XI && (xs == 0 ? nbW : nbE);
+        ge[n] = wx[n] ? gx_at(xl, j0 + xr, xs == 0 ? xi - 1 : xi) : T(0);
+        if constexpr (JAC) {
+            const LayerCoef<T> L = layer(xl);
+            const int j = j0 + xr;
+            const T d = L.sink + gx_at(xl, j, xi - 1) + gx_at(xl, j, xi) + gy_at(xl, j - 1, xi) + gy_at(xl, j, xi) +
+                        L.gzd + L.gzu;
+            de[n] = wx[n] && in_grid(j, xi) && xl < nz ? recip(d) : T(0);
+        }
+        xe[n] = T(0);
+        x_at[n] = (xs * NR + row0 + xr) * NZ + xl;
+        x_row[n] = ((row0 + xr) * NZ + xl) * RS + (xs == 0 ? 0 : kWave - 1);
+        side_at[n] = 8u * (unsigned)((row0 * NZ + xr * NZ + xl) * WT);
     }
-    T xe = T(0);
-    const int x_at = (xs * NR + row0 + xr) * NZ + xl;                                   // its slot in cx
-    const int x_row = ((row0 + xr) * NZ + xl) * RS + (xs == 0 ? 0 : kWave - 1);          // ... and in LDS copy 0
     const bool x_edge = (lane == 0 && nbW) || (lane == kWave - 1 && nbE);   // lanes with an x face to another tile
     const int c_at = ((lane == 0 ? 0 : NR) + row0) * NZ;                    // their corrections in cx
     // the layers' constants, uniform: one scalar register each (LDS reads of them,
@@ -379,7 +393,6 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
     auto word = [&](unsigned bytes) -> u64 * {
         return reinterpret_cast<u64 *>(reinterpret_cast<char *>(ra.buf) + (size_t)bytes);
     };
-    const unsigned side_at = 8u * (unsigned)((row0 * NZ + xr * NZ + xl) * WT);
     const unsigned y_lane = 8u * (unsigned)(lane * WT);
 
     // own rows of z into LDS copy `buf`
@@ -409,10 +422,12 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
         }
         // x edges, one value per lane; the west neighbour reads its east side
         // (after SX), and the reverse
-        if (wx)
-            put_value(word(pb + (unsigned)(xs == 0 ? slot - 1 : slot + 1) * kTileBytes +
-                           8u * (2 * SY + (xs == 0 ? SX : 0)) + side_at),
-                      xe, tag);
+#pragma unroll
+        for (int n = 0; n < XN; ++n)
+            if (wx[n])
+                put_value(word(pb + (unsigned)(xs == 0 ? slot - 1 : slot + 1) * kTileBytes +
+                               8u * (2 * SY + (xs == 0 ? SX : 0)) + side_at[n]),
+                          xe[n], tag);
     };
     auto value = [&](const u64(&g)[WT]) -> T {
         unsigned wd[WT];
@@ -449,18 +464,20 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
         // time, for want of registers (all at once spill in FP64 from 12 layers on:
         // 390x270x14 200 -> 540 us an application).
         constexpr int GL = sizeof(T) == 4 && NZ % 4 == 0 && VY == 1 ? 4 : 2, IL = NZ * 3 / 4 / GL * GL;
-        constexpr int LC = sizeof(T) == 8 ? (NZ == 8 ? 8 : 4) : VY == 1 || NZ * (PC ? 4 : 3) * (JAC ? 4 : 3) < 16 * 4 * 3 ? NZ : NZ / 2;
+        constexpr int LC = sizeof(T) == 8 ? (NZ == 8 ? 8 : 4) : VY == 1 || (NZ <= 16 && NZ * (PC ? 4 : 3) * (JAC ? 4 : 3) < 16 * 4 * 3) ? NZ : NZ / 2;
         const unsigned tag = epoch + (unsigned)(j - 1);
         unsigned own = (unsigned)((j - 1) & 1) * par_bytes + (unsigned)slot * kTileBytes;
         asm volatile("" : "+s"(own));   // (as row_at)
-        const u64 *const qx = word(own + 8u * (2 * SY + (xs == 0 ? 0 : SX)) + side_at);
+        const unsigned qx = own + 8u * (2 * SY + (xs == 0 ? 0 : SX));
         const u64 *const qy = word(own + (w == 0 ? 0u : 8u * SY) + y_lane);
-        u64 wy[LC][WT], wxv[WT] = {};
+        u64 wy[LC][WT], wxv[XN][WT] = {};
         auto poll_x = [&]() {
-            if (wx) {
 #pragma unroll
-                for (int n = 0; n < WT; ++n) wxv[n] = get_word(qx + n);
-            }
+            for (int m = 0; m < XN; ++m)
+                if (wx[m]) {
+#pragma unroll
+                    for (int n = 0; n < WT; ++n) wxv[m][n] = get_word(word(qx + side_at[m]) + n);
+                }
         };
         auto poll_y = [&](int lc) {
 #pragma unroll
@@ -560,15 +577,19 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
         // ---- the faces to other tiles
         left = ra.spin;
         const bool edge_y = edgeS || edgeN;
-        T xc = T(0);   // the x-edge cell's correction
+        T xc[XN] = {};   // the x-edge cells' corrections
 #pragma unroll
         for (int lc = 0; lc < NZ; lc += LC) {
             if (lc > 0 && edge_y) poll_y(lc);
             for (;;) {
                 unsigned off = 0;   // any bit by which a word's tag differs
-                if (lc == 0 && wx) {
+                if (lc == 0) {
 #pragma unroll
-                    for (int n = 0; n < WT; ++n) off |= (unsigned)(wxv[n] >> 32) ^ tag;
+                    for (int m = 0; m < XN; ++m)
+                        if (wx[m]) {
+#pragma unroll
+                            for (int n = 0; n < WT; ++n) off |= (unsigned)(wxv[m][n] >> 32) ^ tag;
+                        }
                 }
                 if (edge_y) {
 #pragma unroll
@@ -581,8 +602,11 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
                 if (edge_y) poll_y(lc);
             }
             if (lc == 0) {
-                xc = c2 * (ge * (value(wxv) - xe));
-                if constexpr (JAC) xc *= de;
+#pragma unroll
+                for (int m = 0; m < XN; ++m) {
+                    xc[m] = c2 * (ge[m] * (value(wxv[m]) - xe[m]));
+                    if constexpr (JAC) xc[m] *= de[m];
+                }
             }
             auto y_face = [&](auto vt) {
                 constexpr int v = decltype(vt)::value;
@@ -604,13 +628,15 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
         }
         wait_loads();
         if (left <= 0) bad_s = 1;   // (any lane may write it: the value is the same)
-        if (wx) {
-            // the x-edge cell itself in the LDS copy, and its correction for the lane that holds it
-            T *q = rows + (x_row + (buf ^ 1) * (NR * NZ * RS));
-            xe = *q + xc;
-            *q = xe;
-            cx[x_at] = xc;
-        }
+#pragma unroll
+        for (int m = 0; m < XN; ++m)
+            if (wx[m]) {
+                // the x-edge cell itself in the LDS copy, and its correction for the lane that holds it
+                T *q = rows + (x_row[m] + (buf ^ 1) * (NR * NZ * RS));
+                xe[m] = *q + xc[m];
+                *q = xe[m];
+                cx[x_at[m]] = xc[m];
+            }
         if (x_edge) {
             constexpr int HV = 16 / sizeof(T);
 #pragma unroll
@@ -657,7 +683,9 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
     };
 
     put_rows(za, 0);
-    if (wx) xe = rows[x_row];
+#pragma unroll
+    for (int n = 0; n < XN; ++n)
+        if (wx[n]) xe[n] = rows[x_row[n]];
     wait_loads();
     send(za, 0);
     __syncthreads();
@@ -734,6 +762,8 @@ bool launch_nz(int nzc, const Args<T> &a) {
     case 8: return launch_one<T, PC, JAC, 8, VY, NW>(a);
     case 12: return launch_one<T, PC, JAC, 12, VY, NW>(a);
     case 16: return launch_one<T, PC, JAC, 16, VY, NW>(a);
+    case 20:
+        if constexpr (sizeof(T) == 4 && VY == 1) return launch_one<T, PC, JAC, 20, VY, NW>(a);
     }
     return false;
 }
@@ -741,6 +771,8 @@ template <typename T, bool PC, bool JAC>
 bool launch_tile(const ResShape &rs, const Args<T> &a) {
     if constexpr (sizeof(T) == 4)
         if (rs.vy == 2 && rs.nw == 8) return launch_nz<T, PC, JAC, 2, 8>(rs.nzc, a);
+    if constexpr (sizeof(T) == 4 && !PC && !JAC)
+        if (rs.vy == 2 && rs.nw == 7 && rs.nzc == 20) return launch_one<T, PC, JAC, 20, 2, 7>(a);
     if (rs.vy == 1 && rs.nw == 8) return launch_nz<T, PC, JAC, 1, 8>(rs.nzc, a);
     if (rs.vy == 1 && rs.nw == 4) return launch_nz<T, PC, JAC, 1, 4>(rs.nzc, a);
     return false;

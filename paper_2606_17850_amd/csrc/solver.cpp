@@ -198,7 +198,10 @@ int device_cus(int device) {
 size_t lds_cap();
 
 // The layer count a lane of the on-chip preconditioner is built for (0: none).
-inline int res_class(int nz) { return nz <= 8 ? 8 : nz <= 12 ? 12 : nz <= 16 ? 16 : 0; }
+template <typename T>
+int res_class(int nz) {
+    return nz <= 8 ? 8 : nz <= 12 ? 12 : nz <= 16 ? 16 : nz <= 20 && sizeof(T) == 4 ? 20 : 0;
+}
 
 // Rows of an ny-row grid as slabs of at most `nty` rows of tiles each, `halo` rows
 // computed twice at every cut (see ResGroup); empty if a slab cannot hold its
@@ -265,12 +268,16 @@ ResShape res_fit(const std::vector<ResDims> &grids, int device, int k) {
     const int cus = device_cus(device);
     int nzc = 0;
     for (const ResDims &g : grids) {
-        if (!res_class(g.nz)) return none;
-        nzc = std::max(nzc, res_class(g.nz));
+        if (!res_class<T>(g.nz)) return none;
+        nzc = std::max(nzc, res_class<T>(g.nz));
     }
-    const std::vector<std::pair<int, int>> shapes =
-        sizeof(T) == 4 ? std::vector<std::pair<int, int>>{{1, 4}, {1, 8}, {2, 8}}
-                       : std::vector<std::pair<int, int>>{{1, 4}, {1, 8}};
+    // (17 to 20 layers: 14 rows are the most the LDS holds, and only the plain FP32
+    // per-layer kernel has the registers for two of them a lane)
+    bool tall = true;
+    for (const ResDims &g : grids) tall = tall && res_class<T>(g.nz) == 20 && !g.cells && !g.jacobi;
+    std::vector<std::pair<int, int>> shapes{{1, 4}, {1, 8}};
+    if (sizeof(T) == 4 && nzc <= 16) shapes.emplace_back(2, 8);
+    if (sizeof(T) == 4 && nzc == 20 && tall) shapes.emplace_back(2, 7);
     ResShape r;
     r.nzc = nzc;
     r.halo = k - 1;
@@ -742,11 +749,11 @@ template <typename T>
 ResPlan make_res_plan(const std::vector<ResDims> &grids, const ResShape &rs, int cus, std::vector<ResGroup> &groups) {
     ResPlan plan;
     groups.clear();
-    for (int nzc : {8, 12, 16}) {
+    for (int nzc : {8, 12, 16, 20}) {
         ResPlan::Launch l{nzc, (int)groups.size(), 0, 0, 0, plan.words, plan.tiles, ResGroup{}};
         for (size_t i = 0; i < grids.size(); ++i) {
             const ResDims &g = grids[i];
-            if (res_class(g.nz) != nzc) continue;
+            if (res_class<T>(g.nz) != nzc) continue;
             const int ntx = tiles_x(g.nx, 1);
             int part0 = 0;
             for (const ResSlab &sl : res_slabs(g.ny, rs.rows(), cus / ntx, rs.halo)) {
@@ -2862,8 +2869,17 @@ Status solve_batch(int nsys, Grid *const *grids, int nrhs, const double *const *
         if (!staged && !ts.bad()) {
             std::vector<Grid *> gs;
             for (Problem *p : ps) gs.push_back(p->g);
-            sh_in.res = mixed ? res_take<float>(gs, sh_in, o.preconditioner, o.cheb_degree, E.res_aborts, lease)
-                              : res_take<double>(gs, sh_in, o.preconditioner, o.cheb_degree, E.res_aborts, lease);
+            // (the tuned shape, or one of more workgroups if it has fewer than a
+            // problem has on-chip tiles)
+            for (const Shape &c : {sh_in, Shape{sh_in.vx, 1, 8}, Shape{sh_in.vx, 1, 4}}) {
+                const ResShape rs =
+                    mixed ? res_take<float>(gs, c, o.preconditioner, o.cheb_degree, E.res_aborts, lease)
+                          : res_take<double>(gs, c, o.preconditioner, o.cheb_degree, E.res_aborts, lease);
+                if (rs.nzc == 0) continue;
+                sh_in = c;
+                sh_in.res = rs;
+                break;
+            }
         }
         if (fuse32 && !ts.bad() && sh_in.res.nzc == 0) {
             const int kk = is_cheb(o.preconditioner) ? o.cheb_degree : 1;
