@@ -48,7 +48,7 @@
  *  - CUTH_RESIDENT=0: never run the whole Chebyshev preconditioner as one
  *    launch with its vectors on chip (default: single solves, and batches except
  *    CUTH_ADAPTIVE ones, of grids of at most 16 layers (FP32: 20), in tiles of 64
- *    columns by 4, 8 or (FP32) 14 or 16 rows of which the device holds one per compute unit at a
+ *    columns by 8 or (FP32) 14 or 16 rows of which the device holds one per compute unit at a
  *    time, in slabs of rows where a grid has more of them and the slabs' overlap
  *    at most doubles the work (FP64: plain Chebyshev on per-cell conductances
  *    only), while no other solve of the process does so on the device;

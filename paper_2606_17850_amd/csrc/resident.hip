@@ -12,11 +12,10 @@
 // where that is long enough).  Per sweep, launches as before -> here: 512x512x16
 // per cell 10.0 -> 2.9 us (256 tiles of 64 x 16 columns: the arithmetic of two
 // wavefronts per SIMD, which issue an instruction every 5.5 cycles each),
-// 256x256x10 4.0 -> 1.8 us, 64x64x8 3.6 -> 1.1 us (the exchange).
+// 256x256x10 4.0 -> 1.5 us, 64x64x8 3.6 -> 1.1 us (the exchange).
 //
-// Tiles.  Small tiles shorten the arithmetic, and below 1024 columns per tile
-// the exchange sets the time, so the host takes the smallest of 64 x 4, 64 x 8
-// and 64 x 16 columns whose tiles the CUs hold one each (res_fit).
+// Tiles.  64 x 8 columns where the CUs hold all such tiles at once, one each, else
+// 64 x 16 (FP32), which do twice the arithmetic per exchange (res_fit).
 //
 // Groups.  Several problems (a batch), or a grid of more tiles than CUs, go
 // through the chip as groups of tiles: a problem is a group, and such a grid is
@@ -29,8 +28,8 @@
 // conductances, launches as before -> here.
 //
 // 17 to 20 layers (FP32) take 14 rows, which fill the LDS, where the plain
-// per-layer kernel fits its registers (255), else 8: 1024x1024x20, 6 slabs, 1190 ->
-// 620 us an application, a backward-Euler step 9.4 -> 6.0 ms (14 slabs of 8-row
+// per-layer kernel fits its registers (255), else 8: 1024x1024x20, 6 slabs, 1490 ->
+// 660 us an application by itself, a backward-Euler step 9.4 -> 6.0 ms (14 slabs of 8-row
 // tiles: 1070 us).
 //
 // FP64.  The same kernel with half the rows per tile.  A value takes two exchange
@@ -774,7 +773,6 @@ bool launch_tile(const ResShape &rs, const Args<T> &a) {
     if constexpr (sizeof(T) == 4 && !PC && !JAC)
         if (rs.vy == 2 && rs.nw == 7 && rs.nzc == 20) return launch_one<T, PC, JAC, 20, 2, 7>(a);
     if (rs.vy == 1 && rs.nw == 8) return launch_nz<T, PC, JAC, 1, 8>(rs.nzc, a);
-    if (rs.vy == 1 && rs.nw == 4) return launch_nz<T, PC, JAC, 1, 4>(rs.nzc, a);
     return false;
 }
 

@@ -245,10 +245,12 @@ int64_t res_tiles(int nx, int ny, const ResShape &rs, int cus) {
 
 // Tile of the on-chip preconditioner for grids of the given sizes, solved
 // together, at degree k (nzc 0: none).  The smallest tile with which the
-// device's CUs hold all of them at once, one tile each: it is the fastest or
-// within a few percent of it (64 x 4, 64 x 8 and 64 x 16 columns take 1.25, 1.24
-// and 1.51 us per sweep at 64x64x8 and 1.88, 1.70 and 2.08 at 256x256x10, where
-// launches take 3.6 and 4.0 us).  What does not fit at once goes through the
+// device's CUs hold all of them at once, one tile each: with 64 x 8 and 64 x 16
+// columns an application takes 67 and 71 us at 64x64x8, 83 and 93 at 128x500x12, 97
+// and 110 at 384x256x16.  (64 x 4 gain nothing where few tiles need few exchanges
+// and crowd them elsewhere: 67 us at 64x64x8, 89 at 128x500x12; a 256x256x10 mixed
+// solve 10.3 ms with 256 tiles of 64 x 4, 9.2 with 128 of 64 x 8.)  What does
+// not fit at once goes through the
 // device in groups of the largest tile, which does the most work per exchange
 // (2.8 us a sweep for 4.2 M unknowns on all CUs, where launches take 8 to 10),
 // as long as the slabs of a grid compute at most twice its own rows.
@@ -275,7 +277,7 @@ ResShape res_fit(const std::vector<ResDims> &grids, int device, int k) {
     // per-layer kernel has the registers for two of them a lane)
     bool tall = true;
     for (const ResDims &g : grids) tall = tall && res_class<T>(g.nz) == 20 && !g.cells && !g.jacobi;
-    std::vector<std::pair<int, int>> shapes{{1, 4}, {1, 8}};
+    std::vector<std::pair<int, int>> shapes{{1, 8}};
     if (sizeof(T) == 4 && nzc <= 16) shapes.emplace_back(2, 8);
     if (sizeof(T) == 4 && nzc == 20 && tall) shapes.emplace_back(2, 7);
     ResShape r;
