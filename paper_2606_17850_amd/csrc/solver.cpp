@@ -751,11 +751,37 @@ template <typename T>
 ResPlan make_res_plan(const std::vector<ResDims> &grids, const ResShape &rs, int cus, std::vector<ResGroup> &groups) {
     ResPlan plan;
     groups.clear();
-    for (int nzc : {8, 12, 16, 20}) {
+    // A launch takes its groups in rounds of all CUs, at least one.  A class whose
+    // tiles do not fill its own rounds joins the next one (its layers padded) where
+    // that is shorter by the classes' times per application: 5 stacks of 128^2 to
+    // 256^2 x 6 to 13, one launch instead of several: 29.1 -> 16.6 ms a solve.
+    const int classes[] = {8, 12, 16, 20}, cost[] = {5, 7, 10, 12};
+    int64_t count[4] = {0, 0, 0, 0};
+    int into[4] = {0, 1, 2, 3};
+    for (const ResDims &g : grids)
+        for (int c = 0; c < 4; ++c)
+            if (classes[c] == res_class<T>(g.nz)) count[c] += res_tiles(g.nx, g.ny, rs, cus);
+    for (int c = 0, next; c < 4; c = next) {
+        for (next = c + 1; next < 4 && count[next] == 0; ++next) {
+        }
+        if (next == 4 || count[c] == 0) continue;
+        auto time = [&](int64_t n, int q) { return (double)std::max<int64_t>(n, cus) * cost[q]; };
+        if (time(count[c] + count[next], next) >= time(count[c], c) + time(count[next], next)) continue;
+        for (int &q : into)
+            if (q == c) q = next;
+        count[next] += count[c];
+        count[c] = 0;
+    }
+    auto class_of = [&](int nz) {
+        for (int c = 0; c < 4; ++c)
+            if (classes[c] == res_class<T>(nz)) return classes[into[c]];
+        return 0;
+    };
+    for (int nzc : classes) {
         ResPlan::Launch l{nzc, (int)groups.size(), 0, 0, 0, plan.words, plan.tiles, ResGroup{}};
         for (size_t i = 0; i < grids.size(); ++i) {
             const ResDims &g = grids[i];
-            if (res_class<T>(g.nz) != nzc) continue;
+            if (class_of(g.nz) != nzc) continue;
             const int ntx = tiles_x(g.nx, 1);
             int part0 = 0;
             for (const ResSlab &sl : res_slabs(g.ny, rs.rows(), cus / ntx, rs.halo)) {
