@@ -162,7 +162,9 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
     // x-edge corrections [2 sides][NR][NZ], then two copies of the tile's rows [2][NR][NZ][RS]
     T *cx = reinterpret_cast<T *>(lds_raw);
     T *rows = cx + 2 * NR * NZ;
-    __shared__ int bad_s;
+    // a wait ran out: sweep j writes entry j & 1 and reads the other, which the barrier
+    // between them has closed (all wavefronts leave in the same sweep)
+    __shared__ int bad_s[2];
 
     int gi = 0;
     {
@@ -187,7 +189,7 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
     int lane = threadIdx.x, w = threadIdx.y, zero = 0;
     asm volatile("" : "+v"(lane), "+v"(w), "+v"(zero));
     w = __builtin_amdgcn_readfirstlane(w);
-    if (tid_lin() == 0) bad_s = 0;
+    if (tid_lin() == 0) bad_s[0] = bad_s[1] = 0;
     const OpView<T> &op = P.op;
     const int nx = op.nx, ny = op.ny, nz = op.nz;
     const int64_t plane = (int64_t)nx * ny;
@@ -449,7 +451,7 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
     // of other wavefronts from LDS copy `buf`, then the faces to other tiles.
     // False when a wait ran out before this sweep.
     auto sweep = [&](const T(&in)[VY][NZ], T(&out)[VY][NZ], int j, int buf) -> bool {
-        const int bad = bad_s;
+        const int bad = bad_s[(j - 1) & 1];
         if (((j - 1) & (kWave - 1)) == 0) {
             const int jl = min(j + lane, k - 1);
             vc1 = gld(P.cheb + 1 + jl);
@@ -626,7 +628,7 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
             if (!edge_y) break;
         }
         wait_loads();
-        if (left <= 0) bad_s = 1;   // (any lane may write it: the value is the same)
+        if (left <= 0) bad_s[j & 1] = 1;   // (any lane may write it: the value is the same)
 #pragma unroll
         for (int m = 0; m < XN; ++m)
             if (wx[m]) {
@@ -666,7 +668,7 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
         const T a = wave_sum(acc);
         if (lane == 0) sh[w] = a;
         __syncthreads();
-        if (bad_s) return false;
+        if (bad_s[0] | bad_s[1]) return false;
         // one partial per tile; the problem's other slots are zero
         for (int q = part + tid_lin() * P.r_ntiles; q < P.ntiles; q += nthreads() * P.r_ntiles) {
             T t = T(0);
