@@ -180,9 +180,15 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
     const InnerProb<T> &P = probs[pidx];
     CgState<T> *st = P.st;
     const int local = slot - G.tile0, part = G.part0 + local;   // tile of the group, of the problem
-    const int done = st->done;
-    if (done) return;
-    if (chk && conv_test(st, part_in, red, pidx, P, part == 0)) return;
+    // The whole workgroup acts on one lane's reading of the stop flag: the problem's
+    // lead tile may set it during this launch, and wavefronts that read it for
+    // themselves could part here and meet different barriers.
+    __shared__ int done_s;
+    int done = 0;
+    if (tid_lin() == 0) done_s = done = st->done;
+    const bool stop = chk && conv_test(st, part_in, red, pidx, P, part == 0 && !done);
+    if (!chk || red) __syncthreads();   // (otherwise the test's sum has had its barriers)
+    if (stop || done_s) return;
 
     // (opaque: what follows from them is not kept in registers over the loop over
     // tiles, and the layers' constants come by vector loads, all in flight at once)
