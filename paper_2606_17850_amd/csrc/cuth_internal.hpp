@@ -96,8 +96,13 @@ inline int red_blocks(int64_t n) {
 }
 
 // Scalars of one PCG run (Algorithm 1) resident on the device.  Kernels never
-// read a field that a workgroup of the same launch writes, except `done`, which
-// every workgroup of a problem sets to the same value from the same data.
+// read a field that a workgroup of the same launch writes, except
+//  - done, which is set to the same value from the same data wherever it is set
+//    (and read once for a workgroup where its wavefronts meet at barriers after);
+//  - gave_up, which tiles of the on-chip preconditioner set from the time they
+//    waited and read while they wait.  It says nothing about that launch's own
+//    test and counts: the next direction kernel (or k_promote_dot) turns it into
+//    done = kResAbort, which later launches see.
 template <typename T>
 struct CgState {
     T rz[2];      // r_k^T z_k in slot k & 1 (direction kernel of k); the host sets
@@ -106,9 +111,11 @@ struct CgState {
     T rr0;        // ||rhat||^2 of the inner right-hand side (host)
     T tol2;       // converged when rr <= tol2 (host)
     T pad;
-    int done;     // 0 running, 1 tolerance, 2 drift, 3 stagnation, 4 breakdown
+    int done;     // 0 running, 1 tolerance, 2 drift, 3 stagnation, 4 breakdown, 5 iteration
+                  // limit, kResAbort an application on chip that gave up
     int iter;     // completed CG iterations (updates followed by a convergence test)
-    int pad2[2];
+    int gave_up;  // tiles of the last application on chip waited in vain: z is not formed
+    int pad2;
 };
 
 // One inner PCG problem (one system and right-hand side) of a batched launch.
@@ -130,10 +137,12 @@ struct InnerProb {
     int r_ntiles = 0, r_ntx = 1;   // tiles of the on-chip preconditioner (launch_cheb_res), r_ntx along x
     // FP64 CG with an FP32 preconditioner (the paper's stage-switched scheme):
     // the update also writes r_lo = (float) r; k_promote_dot reads the
-    // preconditioner's z_lo; k_reduce_conv mirrors the stop flag to *done_lo.
+    // preconditioner's z_lo and *gave_up_lo; k_reduce_conv mirrors the stop flag
+    // to *done_lo.
     float *r_lo = nullptr;
     const float *z_lo = nullptr;
     int *done_lo = nullptr;
+    const int *gave_up_lo = nullptr;
 };
 
 // One FP64 outer-residual problem of a batched launch:
@@ -221,7 +230,7 @@ struct ResGroup {
     int y0, own0, own1;
     int pad;
 };
-constexpr int kResAbort = 6;       // CgState::done of a problem whose tiles waited in vain for a neighbour
+constexpr int kResAbort = 6;       // CgState::done after an application that gave up (CgState::gave_up)
 // Device buffers of one launch of the on-chip preconditioner: its groups, two
 // sweep parities of `tiles` tiles of edge words, and each tile's tag epoch.
 // width: workgroups of the launch, no fewer than any group has tiles and no more

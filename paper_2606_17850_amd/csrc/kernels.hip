@@ -1131,12 +1131,17 @@ __global__ __launch_bounds__(512) void k_dir_b(const InnerProb<T> *__restrict__ 
     const int pidx = find_prob(probs, nprob, slot);
     const InnerProb<T> &P = probs[pidx];
     CgState<T> *st = P.st;
-    const int done = st->done;
+    const int done = st->done, gave_up = st->gave_up;
     const T rz_prev = st->rz[1 - par];
     const T rz = prev_sum(part_in, red, pidx, P);
     if (done) return;
     const bool bad = !(rz > T(0)) || !finite_val(rz);
     const bool lead = (slot == P.tile0) && tid_lin() == 0;
+    // an on-chip preconditioner that gave up left no z: stop this problem here
+    if (gave_up) {
+        if (lead) st->done = kResAbort;
+        return;
+    }
     if (lead) {
         st->rz[par] = rz;
         if (bad) st->done = 4;
@@ -1308,8 +1313,8 @@ __global__ __launch_bounds__(512) void k_promote_dot(const InnerProb<T> *__restr
     const int pidx = find_prob(probs, nprob, slot);
     const InnerProb<T> &P = probs[pidx];
     if (P.st->done) return;
-    // an on-chip preconditioner that gave up left no z: stop this problem here
-    if (P.done_lo && *P.done_lo == kResAbort) {
+    // (as in k_dir_b)
+    if (P.gave_up_lo && *P.gave_up_lo) {
         if (slot == P.tile0 && tid_lin() == 0) P.st->done = kResAbort;
         return;
     }

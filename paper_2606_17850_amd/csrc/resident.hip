@@ -53,10 +53,11 @@
 // Waiting.  Every tile of a group must be running for its neighbours to make
 // progress.  The host launches at most one workgroup per CU and lets one such
 // launch at a time onto a device; every wait is bounded all the same
-// (ResArgs::spin polls): a tile that gives up marks its problem (CgState::done =
-// kResAbort) and ends, its neighbours see the mark and end too, and the host
+// (ResArgs::spin polls): a tile that gives up marks its problem (CgState::gave_up)
+// and ends, its neighbours see the mark while they wait and end too, and the host
 // repeats the application with ordinary launches, which only read r (of several
-// problems: the whole solve of those marked).
+// problems: the whole solve of those marked).  Tiles that start after the mark run
+// all the same: the problem's lead tile counts the iteration, whenever it starts.
 #include "device_util.hpp"
 
 namespace cuth {
@@ -448,7 +449,7 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
     auto waited_out = [&]() -> bool {   // one more poll; true when the bound is reached
         if (--left <= 0) return true;
         if ((left & 255) == 0 &&
-            __hip_atomic_load(&st->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kResAbort)
+            __hip_atomic_load(&st->gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
             left = 1;
         return false;
     };
@@ -714,7 +715,7 @@ __device__ __forceinline__ void res_tile(const InnerProb<T> *__restrict__ probs,
         __syncthreads();
     }
     if (!ok && tid_lin() == 0)
-        __hip_atomic_store(&st->done, (int)kResAbort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&st->gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Tiles blockIdx.x, blockIdx.x + gridDim.x, ... in turn.  All workgroups run at

@@ -1147,14 +1147,14 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, in
         CUTH_HIP(hipMemcpyAsync(E.h_part, eslot<T>(E, P_CHK), sizeof(T) * 2 * (size_t)nb,
                                 hipMemcpyDeviceToHost, s));
         CUTH_TRY(sync_stream(s));
-        if (sh.res.nzc > 0 && nprob == 1 && hs[0].done == kResAbort) {
+        if (sh.res.nzc > 0 && nprob == 1 && hs[0].gave_up) {
             // (a single problem) the tiles of an on-chip application waited in
             // vain for each other: x and r are those after st.iter iterations,
             // z is repeated from r with sweep launches and the iteration goes on
             res_failed(E);
             sh.res = ResShape{};
             graph = false;
-            hs[0].done = 0;
+            hs[0].done = hs[0].gave_up = 0;
             CUTH_HIP(hipMemcpyAsync(Sel<T>::ds(E), hs, sizeof(CgState<T>), hipMemcpyHostToDevice, s));
             it = hs[0].iter;
             --nchecks;
@@ -1181,8 +1181,8 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, in
             p.true_rr = a;
             const double tn = std::sqrt(a);
             const double ln = std::sqrt((double)hs[n].rr);
-            const int why = stop_rule(hs[n].done, tn, std::sqrt(b), ln, p.true_prev, p.low_prev,
-                                      !p.fixed32, it >= maxit);
+            const int why = stop_rule(hs[n].gave_up ? kResAbort : hs[n].done, tn, std::sqrt(b), ln, p.true_prev,
+                                      p.low_prev, !p.fixed32, it >= maxit);
             if (why && !hs[n].done) {
                 // stop this problem on the device too (its launches exit early)
                 hs[n].done = why;
@@ -1526,6 +1526,7 @@ Status inner_solve_staged(Engine &E, std::vector<Problem *> &ps, const Shape &sh
         h64[n].r_lo = p.w32.r;
         h64[n].z_lo = zfin32 == 0 ? p.w32.zA : p.w32.zB;
         h64[n].done_lo = &E.st32[n].done;
+        h64[n].gave_up_lo = &E.st32[n].gave_up;
     }
     CUTH_HIP(hipMemcpyAsync(E.in32, E.h_in32, sizeof(InnerProb<float>) * nprob, hipMemcpyHostToDevice, s));
     CUTH_HIP(hipMemcpyAsync(E.in64, E.h_in64, sizeof(InnerProb<double>) * nprob, hipMemcpyHostToDevice, s));
@@ -1584,7 +1585,7 @@ Status inner_solve_staged(Engine &E, std::vector<Problem *> &ps, const Shape &sh
             zfin32 = precond_final(k, pm, fuse_for<float>(sh32, pm));
             h64[0].z_lo = zfin32 == 0 ? ps[which[0]]->w32.zA : ps[which[0]]->w32.zB;
             hs[0].done = 0;
-            hs32[0].done = 0;
+            hs32[0].done = 0;   // (the host's copy never sees gave_up)
             CUTH_HIP(hipMemcpyAsync(E.in64, h64, sizeof(InnerProb<double>), hipMemcpyHostToDevice, s));
             CUTH_HIP(hipMemcpyAsync(E.st64, hs, sizeof(CgState<double>), hipMemcpyHostToDevice, s));
             CUTH_HIP(hipMemcpyAsync(E.st32, hs32, sizeof(CgState<float>), hipMemcpyHostToDevice, s));
@@ -3057,7 +3058,7 @@ static Status precond_typed(Grid &g, Setup &su, Work<T> &w, const Shape &sh, con
                                        false, false, g.stream, nullptr);
     if (got != zfin) return Status::err(CUTH_E_DEVICE, "internal: preconditioner buffer mismatch");
     CUTH_HIP(hipGetLastError());
-    // (the caller looks at the stop flag of an on-chip application)
+    // (the caller looks at the mark of an on-chip application)
     if (sh.res.nzc > 0)
         CUTH_HIP(hipMemcpyAsync(hs, Sel<T>::ds(E), sizeof(CgState<T>), hipMemcpyDeviceToHost, g.stream));
     return sync_stream(g.stream);
@@ -3125,7 +3126,7 @@ Status precond_apply(Grid &g, double dt, int precision, int pm, double lmin, dou
         sh32.res = precond_res<float>(g, g.sh32, std::max(cc.k, 1), res_take<float>({&g}, sh32, pm, cc.k, g.eng.res_aborts, lease));
         st = precond_typed<float>(g, *su, g.w32, sh32, cc, pm, precision == CUTH_MIXED16,
                                   (const float *)r, (float *)z);
-        if (st.bad() || sh32.res.nzc == 0 || g.eng.h_st32->done != kResAbort) return st;
+        if (st.bad() || sh32.res.nzc == 0 || !g.eng.h_st32->gave_up) return st;
         res_failed(g.eng);
         sh32.res = ResShape{};
         return precond_typed<float>(g, *su, g.w32, sh32, cc, pm, precision == CUTH_MIXED16,
@@ -3136,7 +3137,7 @@ Status precond_apply(Grid &g, double dt, int precision, int pm, double lmin, dou
     ResLease lease;
     sh64.res = precond_res<double>(g, g.sh64, std::max(cc.k, 1), res_take<double>({&g}, sh64, pm, cc.k, g.eng.res_aborts, lease));
     st = precond_typed<double>(g, *su, g.w64, sh64, cc, pm, false, (const double *)r, (double *)z);
-    if (st.bad() || sh64.res.nzc == 0 || g.eng.h_st64->done != kResAbort) return st;
+    if (st.bad() || sh64.res.nzc == 0 || !g.eng.h_st64->gave_up) return st;
     res_failed(g.eng);
     return precond_typed<double>(g, *su, g.w64, g.sh64, cc, pm, false, (const double *)r, (double *)z);
 }
@@ -3250,11 +3251,11 @@ static Status precond_noalloc_typed(Grid &g, double dt, const ChebConsts &cc, in
     if (got != zfin) return Status::err(CUTH_E_DEVICE, "internal: preconditioner buffer mismatch");
     CUTH_HIP(hipGetLastError());
     if (sh.res.nzc > 0) {
-        // the stop flag, into the grid's own pinned state
+        // the mark, into the grid's own pinned state
         CgState<T> *const hs = Sel<T>::hs(g.eng);
         CUTH_HIP(hipMemcpyAsync(hs, Sel<T>::ds(E), sizeof(CgState<T>), hipMemcpyDeviceToHost, g.stream));
         CUTH_TRY(sync_stream(g.stream));
-        aborted = hs->done == kResAbort;
+        aborted = hs->gave_up != 0;
         return Status::ok();
     }
     return sync_stream(g.stream);

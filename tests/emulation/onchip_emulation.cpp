@@ -257,7 +257,7 @@ struct Set {
         };
         emu::run(width, 8, res_lds<float>(8, 1, 8), rng, pick);
     }
-    static bool marked(const CgState<float> &st) { return st.done == kResAbort; }
+    static bool marked(const CgState<float> &st) { return st.gave_up != 0; }
     // z of problem p against the recurrence in 64 bits
     void check(int p) {
         const int nx = ntx * 64;
@@ -324,6 +324,11 @@ int main(int argc, char **argv) {
         expect(Set::marked(s.st[0]), "the mark of a problem given up");
         expect(!Set::marked(s.st[1]) && s.st[1].iter == 7, "the problem after one given up");
         s.check(1);
+    } else if (what == "late_lead") {   // the lead tile starts after the other one has given up
+        Set s(2, 1);
+        s.launch(2, 300, rng, [&](int b, int) { return b == 1 || Set::marked(s.st[0]); });
+        expect(Set::marked(s.st[0]), "the mark of a problem given up");
+        expect(s.st[0].iter == 7 && s.st[0].rr == 2.f, "the update before the application is not counted");
     }
     std::printf("%s\n", emu::g_error.empty() ? "ok" : emu::g_error.c_str());
     return 0;

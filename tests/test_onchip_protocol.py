@@ -74,3 +74,10 @@ def test_a_mark_parts_no_workgroup(emulation, seed):
     """A tile gives up while wavefronts of a neighbour start: they leave together, and
     the problem that the workgroups take next is sound."""
     assert _run(emulation, "gave_up", seed) == "ok"
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_late_lead_tile_counts_the_iteration(emulation, seed):
+    """The solve goes on from the count of updates, also where the tile that counts
+    them starts after another has given up."""
+    assert _run(emulation, "late_lead", seed) == "ok"
