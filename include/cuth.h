@@ -53,8 +53,10 @@
  *    at most doubles the work (FP64: plain Chebyshev on per-cell conductances
  *    only), while no other solve of the process does so on the device;
  *    CUTH_FUSE or CUTH_FUSE3 set, or kernel timing on, asks for sweep launches).
- *    CUTH_RESIDENT_SPIN=<n>: polls its tiles wait for each other before the
- *    application is repeated with sweep launches (default 32768).
+ *    CUTH_RESIDENT_SPIN=<n>[@<m>]: polls its tiles wait for each other before
+ *    the application is repeated with sweep launches (default 32768); with @<m>
+ *    from application m of an inner solve on (launches replayed from graphs keep
+ *    the bound of their capture).
  *  - CUTH_AUTOTUNE_CACHE=<file>: keep the tuned tile shapes of batches there.
  *  - CUTH_GRAPH=0/1: replay CG chunks from captured HIP graphs, kept by the
  *    handle between solves (default: batches, and single solves of grids of

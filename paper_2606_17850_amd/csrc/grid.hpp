@@ -103,6 +103,7 @@ struct Engine {
     ResPlan res_plan;
     bool res_ready = false;
     int res_aborts = 0;   // applications that gave up
+    int res_applied = 0;  // applications enqueued since res_prepare
     hipStream_t own = nullptr;                   // stream for graph capture
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
     // instantiated chunks of CG iterations, by launch configuration: a chunk's

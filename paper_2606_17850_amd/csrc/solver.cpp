@@ -148,11 +148,13 @@ constexpr int64_t kGraphMaxN = int64_t(1) << 21;
 // Polls a wait of the on-chip preconditioner may take (a poll takes 0.5 us or
 // more, a wait in earnest one to a few polls).
 constexpr int kResSpin = 1 << 15;
-// (CUTH_RESIDENT_SPIN=<n> sets another bound: the tests of the way back)
-int res_spin() {
+// (CUTH_RESIDENT_SPIN=<n>[@<m>] sets another bound, from application m of an inner
+// solve on: the tests of the way back)
+int res_spin(int application) {
     const char *e = std::getenv("CUTH_RESIDENT_SPIN");
     const int v = e ? std::atoi(e) : 0;
-    return v > 0 ? v : kResSpin;
+    const char *at = e ? std::strchr(e, '@') : nullptr;
+    return v > 0 && (!at || application >= std::atoi(at + 1)) ? v : kResSpin;
 }
 
 // The right to launch on-chip preconditioners on a device.  All tiles of such a
@@ -741,7 +743,7 @@ ResArgs res_args(const Engine &E, size_t q) {
     a.ngroups = l.gn;
     a.tiles = l.tiles;
     a.width = l.width;
-    a.spin = res_spin();
+    a.spin = res_spin(E.res_applied);
     return a;
 }
 
@@ -891,6 +893,7 @@ Status res_prepare(Engine &E, const std::vector<Problem *> &ps, const Shape &sh,
         E.res_plan = plan;
         E.res_ready = true;
     }
+    E.res_applied = 0;
     return Status::ok();
 }
 
@@ -917,6 +920,7 @@ int enqueue_precond(Engine &E, int nprob, int nb, bool pc, int cs, int pm, const
             (void)launch_cheb_res<T>(rs, d, pc, jac, k, 1, chk && !z1, rr_in, red, eslot<T>(E, P_CHEB),
                                      res_args(E, q), s);
         }
+        ++E.res_applied;
         if (red) launch_reduce_b<T>(d, nprob, eslot<T>(E, P_CHEB), red_rz<T>(E), s);
         return 1;
     }
@@ -1157,9 +1161,12 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, in
             hs[0].done = hs[0].gave_up = 0;
             CUTH_HIP(hipMemcpyAsync(Sel<T>::ds(E), hs, sizeof(CgState<T>), hipMemcpyHostToDevice, s));
             it = hs[0].iter;
-            --nchecks;
-            zfin = enqueue_precond<T>(E, nprob, nb, pc, cs, pm, sh, k, false, red, s, nullptr);
-            continue;
+            if (it < maxit) {
+                --nchecks;
+                zfin = enqueue_precond<T>(E, nprob, nb, pc, cs, pm, sh, k, false, red, s, nullptr);
+                continue;
+            }
+            // (at the iteration limit no z is needed, and this check is the last)
         }
         if (prof && prof->prof) {
             // a stop found on the device at CG iteration t (st.iter = t + 1, or
@@ -1590,9 +1597,11 @@ Status inner_solve_staged(Engine &E, std::vector<Problem *> &ps, const Shape &sh
             CUTH_HIP(hipMemcpyAsync(E.st64, hs, sizeof(CgState<double>), hipMemcpyHostToDevice, s));
             CUTH_HIP(hipMemcpyAsync(E.st32, hs32, sizeof(CgState<float>), hipMemcpyHostToDevice, s));
             it = hs[0].iter;
-            --nchecks;
-            precond();
-            continue;
+            if (it < maxit) {
+                --nchecks;
+                precond();
+                continue;
+            }
         }
         bool all_done = true;
         for (int n = 0; n < nprob; ++n) {
