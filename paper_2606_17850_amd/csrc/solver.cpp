@@ -1113,6 +1113,9 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, in
     if (graph) CUTH_TRY(chunk_graph(period, exec));
     std::vector<double> sums(2 * (size_t)nprob, 0.0);
     int it = 0, nchecks = 0;
+    // of a solve whose application gave up: applications on chip, that one
+    // included, and how often it was repeated
+    int on_chip = 0, repeated = 0;
     Status result = Status::ok();
     // one more host check where the last inner solve of this cycle on this
     // operator stopped: a stop found on the device is only seen at the next
@@ -1161,8 +1164,10 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, in
             hs[0].done = hs[0].gave_up = 0;
             CUTH_HIP(hipMemcpyAsync(Sel<T>::ds(E), hs, sizeof(CgState<T>), hipMemcpyHostToDevice, s));
             it = hs[0].iter;
+            on_chip = 1 + it;
             if (it < maxit) {
                 --nchecks;
+                ++repeated;
                 zfin = enqueue_precond<T>(E, nprob, nb, pc, cs, pm, sh, k, false, red, s, nullptr);
                 continue;
             }
@@ -1230,9 +1235,10 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, in
         p.reason = reason;
         p.drift_stops += reason == 2;
         p.stag_stops += reason == 3;
-        const int fused = fuse_for<T>(sh_in, p.pm);
-        p.bytes += precs_run * by.precond(k, p.pm, fused) * N + iters * (by.dir() + by.update()) * N +
-                   nchecks * by.check() * N;
+        if (sh.res.nzc > 0) on_chip = precs_run;
+        const int launched = precs_run + repeated - on_chip;
+        p.bytes += (on_chip * by.precond(k, p.pm, 4) + launched * by.precond(k, p.pm, fuse_for<T>(sh, p.pm))) * N +
+                   iters * (by.dir() + by.update()) * N + nchecks * by.check() * N;
         p.stencils += (int64_t)precs_run * (k - 1) + iters + nchecks;
         p.last_red = p.rr0 > 0 ? std::sqrt(p.true_rr / p.rr0) : 0.0;
         p.cycles += 1;
@@ -1562,7 +1568,7 @@ Status inner_solve_staged(Engine &E, std::vector<Problem *> &ps, const Shape &sh
         if (red) launch_reduce_b<double>(d, nprob, eslot<double>(E, P_CHEB), red_rz<double>(E), s);
     };
     precond();
-    int it = 0, nchecks = 0;
+    int it = 0, nchecks = 0, on_chip = 0, repeated = 0;   // (as in inner_solve)
     while (it < maxit) {
         const int cnt = std::min(period, maxit - it);
         for (int q = 0; q < cnt; ++q) {
@@ -1597,8 +1603,10 @@ Status inner_solve_staged(Engine &E, std::vector<Problem *> &ps, const Shape &sh
             CUTH_HIP(hipMemcpyAsync(E.st64, hs, sizeof(CgState<double>), hipMemcpyHostToDevice, s));
             CUTH_HIP(hipMemcpyAsync(E.st32, hs32, sizeof(CgState<float>), hipMemcpyHostToDevice, s));
             it = hs[0].iter;
+            on_chip = 1 + it;
             if (it < maxit) {
                 --nchecks;
+                ++repeated;
                 precond();
                 continue;
             }
@@ -1645,8 +1653,10 @@ Status inner_solve_staged(Engine &E, std::vector<Problem *> &ps, const Shape &sh
         p.reason = reason;
         p.drift_stops += reason == 2;
         p.stag_stops += reason == 3;
-        p.bytes += precs_run * (b32.precond(k, p.pm, fuse_for<float>(sh32_in, p.pm)) + 20.0) * N + iters * (dir64 + b64.update() + 4.0) * N +
-                   nchecks * b64.check() * N;
+        if (sh32.res.nzc > 0) on_chip = precs_run;
+        const int launched = precs_run + repeated - on_chip;
+        p.bytes += (on_chip * b32.precond(k, p.pm, 4) + launched * b32.precond(k, p.pm, fuse_for<float>(sh32, p.pm))) * N +
+                   precs_run * 20.0 * N + iters * (dir64 + b64.update() + 4.0) * N + nchecks * b64.check() * N;
         p.stencils += (int64_t)precs_run * (k - 1) + iters + nchecks;
         p.last_red = p.rr0 > 0 ? std::sqrt(p.true_rr / p.rr0) : 0.0;
         p.cycles += 1;

@@ -89,3 +89,30 @@ def test_give_up_at_the_iteration_limit():
     # differs in its FP32 rounding, far below a hundredth of the residual)
     want = last_reduction(CUTH_RESIDENT="0")
     assert want > 0.0 and last_reduction(CUTH_RESIDENT_SPIN="1@3") == pytest.approx(want, rel=1e-2)
+
+
+@pytest.mark.parametrize("precision", ["mixed", "adaptive", "fp64"])
+@pytest.mark.parametrize("m", [0, 4])
+def test_bytes_are_those_of_the_launches_that_ran(monkeypatch, precision, m):
+    """The solve's algorithmic bytes once application m has given up, against a solve
+    by single sweep launches.  Per iteration and cycle they differ by the m + 1
+    applications on chip (at most 5 of more than 20) and, FP32 aside, no more; what
+    an iteration of the sound on-chip solve moves is below a third."""
+    monkeypatch.setenv("CUTH_GRAPH", "0")
+    st = ragged_stack(200, 100, LAYERS[:10], mult=True)
+    g, P = grid_of(st), t64(_power(st))
+
+    def per_iter():
+        s = g.solve(P, precision=precision)[1]
+        assert s["cg_iters"] > 20
+        return s["alg_bytes"] / s["cg_iters"]
+
+    sound = per_iter()
+    monkeypatch.setenv("CUTH_RESIDENT_SPIN", f"1@{m}")
+    say(f"bytes after giving up at application {m}: {precision}")
+    gave_up = per_iter()
+    monkeypatch.setenv("CUTH_FUSE", "0")
+    sweeps = per_iter()
+    assert sound < sweeps / 3
+    assert gave_up == pytest.approx(sweeps, rel=0.05 + 5.0 * (m + 1) / 100)
+    g.close()
