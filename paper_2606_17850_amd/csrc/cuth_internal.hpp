@@ -259,9 +259,10 @@ void launch_res_clear(unsigned long long *buf, size_t words, size_t tiles, hipSt
 // All sweeps 1 .. k - 1 of the Chebyshev preconditioner in one launch over ra.tiles
 // tiles, with every sweep vector on chip: z[zout] = q(A) r and the partials of
 // r^T z (k >= 2).  chk: the convergence test first, as launch_cheb_b.  jac: the
-// Jacobi-scaled sweeps from z_1 in z[0] (zout not 0).  FP16-stored lateral
+// Jacobi-scaled sweeps (zout not 0; z_1 in z[0] with FP16-stored conductances, else
+// formed by the kernel).  FP16-stored lateral
 // conductances are used where op.hx is set.  False if there is no kernel of
-// this shape.
+// this shape (without probs it only says so).
 template <typename T>
 bool launch_cheb_res(const ResShape &rs, const InnerProb<T> *probs, bool pc, bool jac, int k, int zout,
                      bool chk, const T *part_in, bool red, T *part_out, const ResArgs &ra, hipStream_t s);

@@ -760,8 +760,9 @@ struct Args {
 
 template <typename T, bool PC, bool JAC, int NZ, int VY, int NW>
 bool launch_one(const Args<T> &a) {
-    hipLaunchKernelGGL((k_cheb_res<T, PC, JAC, NZ, VY, NW>), dim3(a.ra.width), dim3(kWave, NW),
-                       res_lds<T>(NZ, VY, NW), a.s, a.probs, a.k, a.zout, a.chk, a.part_in, a.red, a.part_out, a.ra);
+    if (a.probs)
+        hipLaunchKernelGGL((k_cheb_res<T, PC, JAC, NZ, VY, NW>), dim3(a.ra.width), dim3(kWave, NW),
+                           res_lds<T>(NZ, VY, NW), a.s, a.probs, a.k, a.zout, a.chk, a.part_in, a.red, a.part_out, a.ra);
     return true;
 }
 template <typename T, bool PC, bool JAC, int VY, int NW>

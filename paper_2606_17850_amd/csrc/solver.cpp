@@ -803,6 +803,17 @@ ResPlan make_res_plan(const std::vector<ResDims> &grids, const ResShape &rs, int
     plan.groups = groups.size();
     return plan;
 }
+// Every launch of a plan has its kernel (res_fit offers no other shape; a launch
+// without one would leave the z of the application before).
+template <typename T>
+Status res_built(const ResPlan &plan, ResShape rs, bool pc, bool jac) {
+    for (const ResPlan::Launch &l : plan.launches) {
+        rs.nzc = l.nzc;
+        if (!launch_cheb_res<T>(rs, nullptr, pc, jac, 2, 1, false, nullptr, false, nullptr, ResArgs{}, nullptr))
+            return Status::err(CUTH_E_DEVICE, "internal: no on-chip kernel of this shape");
+    }
+    return Status::ok();
+}
 // 64-bit words a plan's edge words and epochs take
 inline size_t res_plan_words(const ResPlan &p) { return p.words + (p.tiles + 1) / 2; }
 
@@ -863,6 +874,7 @@ Status res_prepare(Engine &E, const std::vector<Problem *> &ps, const Shape &sh,
     if (dims.empty()) return Status::ok();
     std::vector<ResGroup> groups;
     const ResPlan plan = make_res_plan<T>(dims, sh.res, device_cus(device), groups);
+    CUTH_TRY(res_built<T>(plan, sh.res, dims[0].cells, dims[0].jacobi));
     const size_t words = res_plan_words(plan);
     if (words > E.res_cap || plan.groups > E.res_gcap) {
         CUTH_TRY(sync_stream(s));
@@ -3186,7 +3198,10 @@ static Status precond_noalloc_typed(Grid &g, double dt, const ChebConsts &cc, in
                                " bytes of scratch, above the " +
                                std::to_string(kNoAllocScratchBytes) + " the library holds per device");
     sh.res = precond_res<T>(g, sh, kcap, sh.res);
-    if (sh.res.nzc > 0) L = noalloc_layout<T>(g, kcap, nb, sh.res);
+    if (sh.res.nzc > 0) {
+        L = noalloc_layout<T>(g, kcap, nb, sh.res);
+        CUTH_TRY(res_built<T>(L.plan, sh.res, g.per_cell, pm == CUTH_PC_CHEBYSHEV_JACOBI));
+    }
     unsigned char *base = nullptr;
     CUTH_HIP(noalloc_scratch(g.device, &base));
     // host images of the small parts

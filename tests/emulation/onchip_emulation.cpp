@@ -329,6 +329,24 @@ int main(int argc, char **argv) {
         s.launch(2, 300, rng, [&](int b, int) { return b == 1 || Set::marked(s.st[0]); });
         expect(Set::marked(s.st[0]), "the mark of a problem given up");
         expect(s.st[0].iter == 7 && s.st[0].rr == 2.f, "the update before the application is not counted");
+    } else if (what == "shapes") {   // <T, per cell, Jacobi>: which of the host's tile shapes have a kernel
+        auto built = [](auto t, bool pc, bool jac) {
+            using T = decltype(t);
+            for (int nzc : {8, 12, 16, 20})
+                for (int v : {18, 28, 27}) {
+                    ResShape rs;
+                    rs.nzc = nzc;
+                    rs.vy = v / 10;
+                    rs.nw = v % 10;
+                    if (launch_cheb_res<T>(rs, nullptr, pc, jac, 2, 1, false, nullptr, false, nullptr, ResArgs{}, nullptr))
+                        std::printf("%d:%d%d%d:%dx%d ", nzc, (int)sizeof(T), pc, jac, v / 10, v % 10);
+                }
+        };
+        for (int q = 0; q < 4; ++q) {
+            built(0.f, q & 1, q >> 1);
+            built(0.0, q & 1, q >> 1);
+        }
+        expect(emu_launches == 0, "a launch without problems");
     }
     std::printf("%s\n", emu::g_error.empty() ? "ok" : emu::g_error.c_str());
     return 0;

@@ -81,3 +81,15 @@ def test_late_lead_tile_counts_the_iteration(emulation, seed):
     """The solve goes on from the count of updates, also where the tile that counts
     them starts after another has given up."""
     assert _run(emulation, "late_lead", seed) == "ok"
+
+
+def test_every_tile_shape_has_a_kernel(emulation):
+    """The shapes that the host chooses from: 64 x 8 columns in every layer class (FP64:
+    up to 16), in FP32 64 x 16 up to 16 layers and, plain per layer, 64 x 14 at 20."""
+    built = _run(emulation, "shapes", 0).split()
+    want = {"ok"}
+    for cells in (0, 1):
+        for jacobi in (0, 1):
+            want |= {f"{nz}:{size}{cells}{jacobi}:1x8" for nz in (8, 12, 16, 20) for size in (4, 8) if nz <= 16 or size == 4}
+            want |= {f"{nz}:4{cells}{jacobi}:2x8" for nz in (8, 12, 16)}
+    assert want | {"20:400:2x7"} == set(built)
