@@ -51,8 +51,13 @@
  *    columns by 8 or (FP32) 14 or 16 rows of which the device holds one per compute unit at a
  *    time, in slabs of rows where a grid has more of them and the slabs' overlap
  *    at most doubles the work (FP64: plain Chebyshev on per-cell conductances
- *    only), while no other solve of the process does so on the device;
- *    CUTH_FUSE or CUTH_FUSE3 set, or kernel timing on, asks for sweep launches).
+ *    only); CUTH_FUSE or CUTH_FUSE3 set, or kernel timing on, asks for sweep
+ *    launches).  Solves of several threads share the device's compute units: one
+ *    that needs more than the others leave waits for them, in the order of arrival,
+ *    so that results do not depend on other threads.  Other processes and other
+ *    work on the device can hold compute units for longer than the bound below;
+ *    the application is then repeated with sweep launches, whose results differ
+ *    in rounding.
  *    CUTH_RESIDENT_SPIN=<n>[@<m>]: polls its tiles wait for each other before
  *    the application is repeated with sweep launches (default 32768); with @<m>
  *    from application m of an inner solve on (launches replayed from graphs keep

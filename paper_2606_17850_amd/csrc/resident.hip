@@ -51,8 +51,8 @@
 // of z_j (double-buffered, so one barrier per sweep suffices).
 //
 // Waiting.  Every tile of a group must be running for its neighbours to make
-// progress.  The host launches at most one workgroup per CU and lets one such
-// launch at a time onto a device; every wait is bounded all the same
+// progress.  The host launches at most one workgroup per CU, over all such launches
+// of the process on the device (ResLease); every wait is bounded all the same
 // (ResArgs::spin polls): a tile that gives up marks its problem (CgState::gave_up)
 // and ends, its neighbours see the mark while they wait and end too, and the host
 // repeats the application with ordinary launches, which only read r (of several

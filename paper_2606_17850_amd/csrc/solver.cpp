@@ -8,9 +8,9 @@
 // Solves of several systems and right-hand sides advance together: each launch
 // covers every active problem (a single solve is a set of one).
 #include "grid.hpp"
+#include "res_lease.hpp"
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -156,32 +156,6 @@ int res_spin(int application) {
     const char *at = e ? std::strchr(e, '@') : nullptr;
     return v > 0 && (!at || application >= std::atoi(at + 1)) ? v : kResSpin;
 }
-
-// The right to launch on-chip preconditioners on a device.  All tiles of such a
-// launch must run at the same time, so at most one solve of the process uses
-// them per device at a time; another solve meanwhile takes the ordinary
-// launches.  (A solve waits for its stream before it returns, so the lease
-// covers all its launches.)
-class ResLease {
-public:
-    ResLease() = default;
-    ResLease(const ResLease &) = delete;
-    ResLease &operator=(const ResLease &) = delete;
-    ~ResLease() {
-        if (held_) held_->clear(std::memory_order_release);
-    }
-    bool acquire(int device) {
-        static std::atomic_flag busy[kDevices];   // (static: cleared)
-        if (device < 0 || device >= kDevices) return false;
-        if (busy[device].test_and_set(std::memory_order_acquire)) return false;
-        held_ = &busy[device];
-        return true;
-    }
-
-private:
-    static constexpr int kDevices = 64;
-    std::atomic_flag *held_ = nullptr;
-};
 
 // CUTH_RESIDENT=0: never use the on-chip preconditioner.  The settings that
 // force or forbid fused sweeps ask for sweep launches, so they rule it out too.
@@ -817,8 +791,8 @@ Status res_built(const ResPlan &plan, ResShape rs, bool pc, bool jac) {
 // 64-bit words a plan's edge words and epochs take
 inline size_t res_plan_words(const ResPlan &p) { return p.words + (p.tiles + 1) / 2; }
 
-// The on-chip shape for grids solved together on one device, where one may be
-// used now (the lease taken); nzc 0 otherwise.
+// The on-chip shape for grids solved together on one device, where there is one
+// (the lease taken, for which this may wait); nzc 0 otherwise.
 template <typename T>
 ResShape res_take(const std::vector<Grid *> &grids, const Shape &sh, int pm, int degree, int aborts, ResLease &lease) {
     if (!is_cheb(pm) || degree < 2 || !res_allowed() || aborts >= kResAborts) return ResShape{};
@@ -828,9 +802,13 @@ ResShape res_take(const std::vector<Grid *> &grids, const Shape &sh, int pm, int
     const ResShape rs = res_fit<T>(dims, device, degree);
     if (rs.nzc == 0) return rs;
     // (one partial sum per tile goes into the sweeps' workgroup slots)
-    for (const Grid *g : grids)
-        if (res_tiles(g->nx, g->ny, rs, device_cus(device)) > prob_tiles(*g, sh)) return ResShape{};
-    return lease.acquire(device) ? rs : ResShape{};
+    int64_t tiles = 0;
+    for (const Grid *g : grids) {
+        const int64_t n = res_tiles(g->nx, g->ny, rs, device_cus(device));
+        if (n > prob_tiles(*g, sh)) return ResShape{};
+        tiles += n;
+    }
+    return lease.acquire(device, tiles, device_cus(device)) ? rs : ResShape{};
 }
 
 // Tiles of the CG kernels for a grid whose preconditioner is on chip (a shape set
@@ -2415,6 +2393,7 @@ Status solve_system(Grid &g, double dt, const double *P, const double *Tn, const
     Status st;
     cuth_options o = o_in;
     if (o.cheb_degree > g.eng.kcap) return Status::err(CUTH_E_INVALID, "cheb_degree above 256");
+    CUTH_TRY(sync_stream(g.stream));   // (before a lease is taken)
     CUTH_HIP(hipEventRecord(g.ev0, g.stream));
     Setup *su = get_setup(g, dt, st);
     if (!su) return st;
@@ -2803,6 +2782,7 @@ Status solve_batch(int nsys, Grid *const *grids, int nrhs, const double *const *
     const bool mixed = o.precision == CUTH_MIXED || o.precision == CUTH_MIXED16 || o.precision == CUTH_FP32;
     const bool staged = o.precision == CUTH_ADAPTIVE;
     const hipStream_t user = grids[0]->stream;
+    CUTH_TRY(sync_stream(user));   // (before a lease is taken)
     // per-system setup (Lanczos bounds cached in each grid)
     std::vector<Setup *> sus(nsys);
     for (int s = 0; s < nsys; ++s) {
@@ -3145,6 +3125,7 @@ Status precond_apply(Grid &g, double dt, int precision, int pm, double lmin, dou
                      int degree, const void *r, void *z) {
     Status st;
     if (degree > g.eng.kcap) return Status::err(CUTH_E_INVALID, "degree above 256");
+    CUTH_TRY(sync_stream(g.stream));   // (before a lease is taken)
     Setup *su = get_setup(g, dt, st);
     if (!su) return st;
     // Jacobi and none are single passes; their degree is 1 (the constants are unused)
@@ -3298,6 +3279,7 @@ static Status precond_noalloc_typed(Grid &g, double dt, const ChebConsts &cc, in
 Status precond_apply_noalloc(Grid &g, double dt, int precision, int pm, double lmin, double lmax,
                              int degree, const void *r, void *z) {
     const ChebConsts cc = make_cheb(lmin, lmax, is_cheb(pm) ? degree : 1);
+    CUTH_TRY(sync_stream(g.stream));   // (before a lease is taken)
     bool aborted = false;
     if (precision != CUTH_FP64) {
         const bool h16 = precision == CUTH_MIXED16;

@@ -1,0 +1,39 @@
+// Threads that take compute units from ResLease (no device): prints "ok" or what
+// went wrong.
+#include "res_lease.hpp"
+
+#include <atomic>
+#include <chrono>
+#include <cstdio>
+#include <random>
+#include <thread>
+#include <vector>
+
+int main() {
+    constexpr int kUnits = 256, kThreads = 8, kTurns = 400;
+    std::atomic<int> held{0}, wide{0}, together{0}, over{0}, refused{0};
+    std::vector<std::thread> threads;
+    for (int t = 0; t < kThreads; ++t)
+        threads.emplace_back([&, t] {
+            std::mt19937 rng(t);
+            const int widths[] = {1, 8, 60, 128, 200, 256, 300};   // (more than there are: all of them)
+            for (int q = 0; q < kTurns; ++q) {
+                const int w = widths[rng() % 7], need = std::min((w + 7) / 8 * 8, kUnits);
+                cuth::ResLease lease;
+                if (!lease.acquire(0, w, kUnits)) ++refused;
+                const int now = held += need;
+                if (now > kUnits) ++over;
+                if (now > need) ++together;
+                if (need == kUnits) ++wide;
+                std::this_thread::sleep_for(std::chrono::microseconds(rng() % 50));
+                held -= need;
+            }
+        });
+    for (auto &t : threads) t.join();
+    cuth::ResLease none;
+    if (over || refused || !together || !wide || none.acquire(-1, 8, kUnits) || none.acquire(64, 8, kUnits))
+        std::printf("over %d refused %d together %d wide %d\n", over.load(), refused.load(), together.load(), wide.load());
+    else
+        std::printf("ok\n");
+    return 0;
+}
