@@ -57,7 +57,8 @@
  *    so that results do not depend on other threads.  Other processes and other
  *    work on the device can hold compute units for longer than the bound below;
  *    the application is then repeated with sweep launches, whose results differ
- *    in rounding.
+ *    in rounding, and a handle that has seen two such keeps to them for its next 8
+ *    calls (16 if it then gives up again, and so on up to 1024).
  *    CUTH_RESIDENT_SPIN=<n>[@<m>]: polls its tiles wait for each other before
  *    the application is repeated with sweep launches (default 32768); with @<m>
  *    from application m of an inner solve on (launches replayed from graphs keep

@@ -102,7 +102,9 @@ struct Engine {
     size_t res_cap = 0, res_gcap = 0;   // words (epochs included) and groups allocated
     ResPlan res_plan;
     bool res_ready = false;
-    int res_aborts = 0;   // applications that gave up
+    int res_aborts = 0;   // applications that gave up since a call without
+    int res_pause = 0;    // calls that keep to sweep launches before the next try
+    int res_wait = 0;     // the last such number
     int res_applied = 0;  // applications enqueued since res_prepare
     hipStream_t own = nullptr;                   // stream for graph capture
     hipEvent_t ev_in = nullptr, ev_out = nullptr;

@@ -45,6 +45,8 @@ public:
         return true;
     }
 
+    bool held() const { return pool_ != nullptr; }
+
 private:
     struct Pool {
         std::mutex mu;

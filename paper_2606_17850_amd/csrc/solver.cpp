@@ -696,14 +696,35 @@ T *red_rr(Engine &E) { return eslot<T>(E, P_RED) + 2 * E.cap; }
 // doubles, past them in either precision)
 double *outer_totals(Engine &E) { return eslot<double>(E, P_RED) + 3 * E.cap; }
 
-// After this many applications that gave up, an engine keeps to sweep launches.
-constexpr int kResAborts = 2;
+// After this many applications that gave up, an engine keeps to sweep launches for
+// the rest of the call and the next kResPause calls; if the next try gives up
+// again, for twice as many (whatever holds the compute units may stay or end).
+constexpr int kResAborts = 2, kResPause = 8, kResPauseMax = 1024;
 // An application gave up: tags and counts are cleared before the next one.
 void res_failed(Engine &E) {
-    ++E.res_aborts;
+    if (++E.res_aborts >= kResAborts)
+        E.res_pause = E.res_wait = std::min(std::max(2 * E.res_wait, kResPause), kResPauseMax);
     E.res_ready = false;
     if (log_on()) std::fprintf(stderr, "cuth: on-chip preconditioner gave up waiting; using sweep launches\n");
 }
+
+// One call's use of the on-chip preconditioner: whether the engine may try it, and
+// the lease that goes with it.
+struct ResCall {
+    Engine &E;
+    const int aborts;
+    bool may = true;
+    ResLease lease;
+    explicit ResCall(Engine &e) : E(e), aborts(e.res_aborts) {
+        if (E.res_pause > 0) {
+            --E.res_pause;
+            may = false;
+        }
+    }
+    ~ResCall() {   // (a call that ran on chip throughout)
+        if (lease.held() && E.res_aborts == aborts) E.res_aborts = E.res_wait = 0;
+    }
+};
 
 ResArgs res_args(const Engine &E, size_t q) {
     const ResPlan &p = E.res_plan;
@@ -794,8 +815,8 @@ inline size_t res_plan_words(const ResPlan &p) { return p.words + (p.tiles + 1) 
 // The on-chip shape for grids solved together on one device, where there is one
 // (the lease taken, for which this may wait); nzc 0 otherwise.
 template <typename T>
-ResShape res_take(const std::vector<Grid *> &grids, const Shape &sh, int pm, int degree, int aborts, ResLease &lease) {
-    if (!is_cheb(pm) || degree < 2 || !res_allowed() || aborts >= kResAborts) return ResShape{};
+ResShape res_take(const std::vector<Grid *> &grids, const Shape &sh, int pm, int degree, ResCall &call) {
+    if (!is_cheb(pm) || degree < 2 || !res_allowed() || !call.may) return ResShape{};
     std::vector<ResDims> dims;
     for (const Grid *g : grids) dims.push_back(ResDims{g->nx, g->ny, g->nz, g->per_cell, pm == CUTH_PC_CHEBYSHEV_JACOBI});
     const int device = grids[0]->device;
@@ -808,7 +829,7 @@ ResShape res_take(const std::vector<Grid *> &grids, const Shape &sh, int pm, int
         if (n > prob_tiles(*g, sh)) return ResShape{};
         tiles += n;
     }
-    return lease.acquire(device, tiles, device_cus(device)) ? rs : ResShape{};
+    return call.lease.acquire(device, tiles, device_cus(device)) ? rs : ResShape{};
 }
 
 // Tiles of the CG kernels for a grid whose preconditioner is on chip (a shape set
@@ -1038,7 +1059,7 @@ template <typename T>
 Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, int k, int maxit,
                    int period, bool use_graph, hipStream_t s, Grid *prof) {
     Shape sh = sh_in;
-    if (sh.res.nzc > 0 && E.res_aborts >= kResAborts) sh.res = ResShape{};
+    if (sh.res.nzc > 0 && E.res_pause > 0) sh.res = ResShape{};
     if (sh.res.nzc > 0) CUTH_TRY(res_prepare<T>(E, ps, sh, s));
     std::vector<int> which;
     const int nb = build_inner<T>(E, ps, sh, which);
@@ -1505,7 +1526,7 @@ Status run_refinement(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in,
 Status inner_solve_staged(Engine &E, std::vector<Problem *> &ps, const Shape &sh32_in,
                           const Shape &sh64, int k, int maxit, int period, hipStream_t s) {
     Shape sh32 = sh32_in;
-    if (sh32.res.nzc > 0 && E.res_aborts >= kResAborts) sh32.res = ResShape{};
+    if (sh32.res.nzc > 0 && E.res_pause > 0) sh32.res = ResShape{};
     if (sh32.res.nzc > 0) CUTH_TRY(res_prepare<float>(E, ps, sh32, s));
     std::vector<int> which32, which;
     const int nb32 = build_inner<float>(E, ps, sh32, which32);
@@ -2455,9 +2476,9 @@ Status solve_system(Grid &g, double dt, const double *P, const double *Tn, const
     const int ge = graph_env();
     const bool use_graph = !g.prof && (ge == 1 || (ge < 0 && g.N <= kGraphMaxN));
     Shape sh32 = g.sh32;
-    ResLease lease;
+    ResCall call(g.eng);
     if (o.precision != CUTH_FP64 && !g.prof)
-        sh32.res = res_take<float>({&g}, sh32, o.preconditioner, o.cheb_degree, g.eng.res_aborts, lease);
+        sh32.res = res_take<float>({&g}, sh32, o.preconditioner, o.cheb_degree, call);
     if (o.precision != CUTH_FP64 && fuse_env() != 0 && sh32.res.nzc == 0) {
         // fused pairs of general sweeps where they are faster on this grid
         CUTH_TRY(alloc_work(g.w32, g.N, true));
@@ -2471,7 +2492,7 @@ Status solve_system(Grid &g, double dt, const double *P, const double *Tn, const
     }
     Shape sh64 = p.csr ? sh_csr : g.sh64;
     if (o.precision == CUTH_FP64 && !p.csr && !g.prof)
-        sh64.res = res_take<double>({&g}, sh64, o.preconditioner, o.cheb_degree, g.eng.res_aborts, lease);
+        sh64.res = res_take<double>({&g}, sh64, o.preconditioner, o.cheb_degree, call);
     Shape outer64 = g.sh64;
     if (sh64.res.nzc > 0) sh64 = cg_shape<double>(g, sh64, g.eng);
     if (sh32.res.nzc > 0) {
@@ -2905,7 +2926,7 @@ Status solve_batch(int nsys, Grid *const *grids, int nrhs, const double *const *
                         ? autotune<float>(E, ps, o.cheb_degree, sig.str() + " in", sh_in)
                         : autotune<double>(E, ps, o.cheb_degree, sig.str() + " in", sh_in);
         if (!mixed && !staged) sh64 = sh_in;
-        ResLease lease;
+        ResCall call(E);
         if (!staged && !ts.bad()) {
             std::vector<Grid *> gs;
             for (Problem *p : ps) gs.push_back(p->g);
@@ -2913,8 +2934,8 @@ Status solve_batch(int nsys, Grid *const *grids, int nrhs, const double *const *
             // problem has on-chip tiles)
             for (const Shape &c : {sh_in, Shape{sh_in.vx, 1, 8}, Shape{sh_in.vx, 1, 4}}) {
                 const ResShape rs =
-                    mixed ? res_take<float>(gs, c, o.preconditioner, o.cheb_degree, E.res_aborts, lease)
-                          : res_take<double>(gs, c, o.preconditioner, o.cheb_degree, E.res_aborts, lease);
+                    mixed ? res_take<float>(gs, c, o.preconditioner, o.cheb_degree, call)
+                          : res_take<double>(gs, c, o.preconditioner, o.cheb_degree, call);
                 if (rs.nzc == 0) continue;
                 sh_in = c;
                 sh_in.res = rs;
@@ -3134,8 +3155,8 @@ Status precond_apply(Grid &g, double dt, int precision, int pm, double lmin, dou
         Shape sh32 = g.sh32;
         set_fuse(sh32, g.nx);
         if (sh32.fr > 0) CUTH_TRY(alloc_work(g.w32, g.N, true));
-        ResLease lease;
-        sh32.res = precond_res<float>(g, g.sh32, std::max(cc.k, 1), res_take<float>({&g}, sh32, pm, cc.k, g.eng.res_aborts, lease));
+        ResCall call(g.eng);
+        sh32.res = precond_res<float>(g, g.sh32, std::max(cc.k, 1), res_take<float>({&g}, sh32, pm, cc.k, call));
         st = precond_typed<float>(g, *su, g.w32, sh32, cc, pm, precision == CUTH_MIXED16,
                                   (const float *)r, (float *)z);
         if (st.bad() || sh32.res.nzc == 0 || !g.eng.h_st32->gave_up) return st;
@@ -3146,8 +3167,8 @@ Status precond_apply(Grid &g, double dt, int precision, int pm, double lmin, dou
     }
     CUTH_TRY(alloc_work(g.w64, g.N));
     Shape sh64 = g.sh64;
-    ResLease lease;
-    sh64.res = precond_res<double>(g, g.sh64, std::max(cc.k, 1), res_take<double>({&g}, sh64, pm, cc.k, g.eng.res_aborts, lease));
+    ResCall call(g.eng);
+    sh64.res = precond_res<double>(g, g.sh64, std::max(cc.k, 1), res_take<double>({&g}, sh64, pm, cc.k, call));
     st = precond_typed<double>(g, *su, g.w64, sh64, cc, pm, false, (const double *)r, (double *)z);
     if (st.bad() || sh64.res.nzc == 0 || !g.eng.h_st64->gave_up) return st;
     res_failed(g.eng);
@@ -3283,18 +3304,18 @@ Status precond_apply_noalloc(Grid &g, double dt, int precision, int pm, double l
     bool aborted = false;
     if (precision != CUTH_FP64) {
         const bool h16 = precision == CUTH_MIXED16;
-        ResLease lease;
-        const ResShape rs = res_take<float>({&g}, g.sh32, pm, cc.k, g.eng.res_aborts, lease);
+        ResCall call(g.eng);
+        const ResShape rs = res_take<float>({&g}, g.sh32, pm, cc.k, call);
         Status st = precond_noalloc_typed<float>(g, dt, cc, pm, h16, (const float *)r, (float *)z, rs, aborted);
         if (st.bad() || !aborted) return st;
-        ++g.eng.res_aborts;
+        res_failed(g.eng);
         return precond_noalloc_typed<float>(g, dt, cc, pm, h16, (const float *)r, (float *)z, ResShape{}, aborted);
     }
-    ResLease lease;
-    const ResShape rs = res_take<double>({&g}, g.sh64, pm, cc.k, g.eng.res_aborts, lease);
+    ResCall call(g.eng);
+    const ResShape rs = res_take<double>({&g}, g.sh64, pm, cc.k, call);
     const Status st = precond_noalloc_typed<double>(g, dt, cc, pm, false, (const double *)r, (double *)z, rs, aborted);
     if (st.bad() || !aborted) return st;
-    ++g.eng.res_aborts;
+    res_failed(g.eng);
     return precond_noalloc_typed<double>(g, dt, cc, pm, false, (const double *)r, (double *)z, ResShape{}, aborted);
 }
 

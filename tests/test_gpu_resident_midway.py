@@ -9,6 +9,7 @@ import sys
 
 import numpy as np
 import pytest
+import torch
 
 from gpu_helpers import grid_of, ragged_stack, rise_err, say, t64
 from paper_2606_17850_amd import solve_batch
@@ -116,3 +117,62 @@ def test_bytes_are_those_of_the_launches_that_ran(monkeypatch, precision, m):
     assert sound < sweeps / 3
     assert gave_up == pytest.approx(sweeps, rel=0.05 + 5.0 * (m + 1) / 100)
     g.close()
+
+
+@pytest.mark.parametrize("precision", ["mixed", "adaptive", "fp64"])
+def test_a_handle_tries_again(monkeypatch, precision):
+    """After two applications that gave up a handle keeps to sweep launches for 8 calls,
+    then runs on chip again; if that gives up at once, for 16."""
+    monkeypatch.setenv("CUTH_GRAPH", "0")
+    st = ragged_stack(200, 100, LAYERS[:10], mult=True)
+    g, P = grid_of(st), t64(_power(st))
+
+    def on_chip():
+        s = g.solve(P, precision=precision)[1]
+        return s["alg_bytes"] / s["cg_iters"] < 1.1 * sound
+
+    s = g.solve(P, precision=precision)[1]
+    sound = s["alg_bytes"] / s["cg_iters"]
+    for pause, gives_up in ((8, 2), (16, 1)):
+        say(f"gives up {gives_up} times, then {pause} calls: {precision}")
+        monkeypatch.setenv("CUTH_RESIDENT_SPIN", "1")
+        for _ in range(gives_up):
+            cycles = g.solve(P, precision=precision, max_outer=20)[1]["outer_cycles"]
+            if cycles > 1:   # (one application gave up in each of two cycles)
+                break
+        monkeypatch.delenv("CUTH_RESIDENT_SPIN")
+        assert not any(on_chip() for _ in range(pause))
+        if pause == 16:
+            assert on_chip() and on_chip()
+    g.close()
+
+
+@pytest.mark.parametrize("precision,dtype", [("mixed", "float32"), ("mixed16", "float32"), ("fp64", "float64")])
+@pytest.mark.parametrize("pc", ["chebyshev", "chebyshev_jacobi"])
+def test_entry_points_repeat_an_application(monkeypatch, precision, dtype, pc):
+    """precond_apply and its allocation-free form, whose tiles give up: what they return
+    by sweep launches, and on chip again after the pause."""
+    st = ragged_stack(200, 100, LAYERS[:10], mult=True)
+    r = torch.as_tensor(np.random.default_rng(3).standard_normal(st.n), dtype=getattr(torch, dtype), device="cuda")
+    for alloc in (True, False):
+        g = grid_of(st)
+        b = g.spectral_bounds(preconditioner=pc)
+
+        def apply():
+            kw = dict(fp16_coef=precision == "mixed16", preconditioner=pc)
+            if alloc:
+                return g.precond_apply(r, b["lmin"], b["lmax"], 12, **kw)
+            return g.precond_apply_noalloc(r, torch.full_like(r, float("nan")), b["lmin"], b["lmax"], 12, **kw)
+
+        sound = apply()
+        monkeypatch.setenv("CUTH_RESIDENT", "0")
+        sweeps = apply()
+        monkeypatch.delenv("CUTH_RESIDENT")
+        assert not torch.equal(sound, sweeps)
+        monkeypatch.setenv("CUTH_RESIDENT_SPIN", "1")
+        say(f"application by itself gives up: {precision} {pc} {'' if alloc else 'no '}alloc")
+        assert torch.equal(apply(), sweeps) and torch.equal(apply(), sweeps)
+        monkeypatch.delenv("CUTH_RESIDENT_SPIN")
+        assert all(torch.equal(apply(), sweeps) for _ in range(8))
+        assert torch.equal(apply(), sound)
+        g.close()
