@@ -850,9 +850,10 @@ Shape cg_shape(const Grid &g, const Shape &def, const Engine &E) {
     } else if (sizeof(T) == 8) {
         s.by = 4;
     }
-    // (as in build_inner: two partials per workgroup; one per on-chip tile)
+    // (partials per workgroup: two in build_inner, kResidualValues where this is the
+    // outer residual's shape too; one per on-chip tile)
     const int64_t n = prob_tiles(g, s);
-    const bool fits = (size_t)n * 2 <= E.slot_doubles &&
+    const bool fits = (size_t)n * kResidualValues <= E.slot_doubles &&
                       (s.res.nzc == 0 || res_tiles(g.nx, g.ny, s.res, device_cus(g.device)) <= n);
     return fits ? s : def;
 }
