@@ -59,6 +59,9 @@
  *    the application is then repeated with sweep launches, whose results differ
  *    in rounding, and a handle that has seen two such keeps to them for its next 8
  *    calls (16 if it then gives up again, and so on up to 1024).
+ *    CUTH_RESIDENT_MB=<n>: device memory in MiB that a handle's (or batch's)
+ *    exchange between tiles may take, about 20 to 80 KiB a tile; above it, or where
+ *    there is no memory for it, sweep launches.
  *    CUTH_RESIDENT_SPIN=<n>[@<m>]: polls its tiles wait for each other before
  *    the application is repeated with sweep launches (default 32768); with @<m>
  *    from application m of an inner solve on (launches replayed from graphs keep

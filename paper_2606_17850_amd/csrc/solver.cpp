@@ -157,6 +157,12 @@ int res_spin(int application) {
     return v > 0 && (!at || application >= std::atoi(at + 1)) ? v : kResSpin;
 }
 
+// CUTH_RESIDENT_MB=<n>: most device memory (MiB) an engine's exchange may take.
+size_t res_limit() {
+    const char *e = std::getenv("CUTH_RESIDENT_MB");
+    return e ? (size_t)std::max(std::atoi(e), 0) << 20 : std::numeric_limits<size_t>::max();
+}
+
 // CUTH_RESIDENT=0: never use the on-chip preconditioner.  The settings that
 // force or forbid fused sweeps ask for sweep launches, so they rule it out too.
 bool res_allowed() {
@@ -861,9 +867,10 @@ Shape cg_shape(const Grid &g, const Shape &def, const Engine &E) {
 // Plan and exchange of the on-chip preconditioner for the problems with p->inner
 // set (in the order of their descriptors) at shape sh.res.  The exchange is
 // cleared if it is new, if a launch gave up, or if tiles may have changed their
-// problem (several groups); outside any capture.
+// problem (several groups); outside any capture.  Without the memory for it
+// sh.res is cleared: sweep launches need none.
 template <typename T>
-Status res_prepare(Engine &E, const std::vector<Problem *> &ps, const Shape &sh, hipStream_t s) {
+Status res_prepare(Engine &E, const std::vector<Problem *> &ps, Shape &sh, hipStream_t s) {
     std::vector<ResDims> dims;
     int device = 0;
     for (const Problem *p : ps)
@@ -878,16 +885,25 @@ Status res_prepare(Engine &E, const std::vector<Problem *> &ps, const Shape &sh,
     const size_t words = res_plan_words(plan);
     if (words > E.res_cap || plan.groups > E.res_gcap) {
         CUTH_TRY(sync_stream(s));
-        // captured chunks hold the old buffers' addresses
-        for (auto &g : E.graphs) (void)hipGraphExecDestroy(g.second);
-        E.graphs.clear();
-        dev_free(E.res_buf);
-        dev_free(E.res_groups);
-        host_free(E.h_res_groups);
-        E.res_cap = E.res_gcap = 0;
-        CUTH_TRY(dev_alloc(&E.res_buf, words));
-        CUTH_TRY(dev_alloc(&E.res_groups, plan.groups));
-        CUTH_TRY(host_alloc(&E.h_res_groups, plan.groups));
+        auto release = [&] {
+            dev_free(E.res_buf);
+            dev_free(E.res_groups);
+            host_free(E.h_res_groups);
+            E.res_cap = E.res_gcap = 0;
+        };
+        if (E.res_buf) {
+            // captured chunks hold the old buffers' addresses
+            for (auto &g : E.graphs) (void)hipGraphExecDestroy(g.second);
+            E.graphs.clear();
+            release();
+        }
+        if (words * sizeof(*E.res_buf) > res_limit() || dev_alloc(&E.res_buf, words).bad() ||
+            dev_alloc(&E.res_groups, plan.groups).bad() || host_alloc(&E.h_res_groups, plan.groups).bad()) {
+            release();
+            sh.res = ResShape{};
+            if (log_on()) std::fprintf(stderr, "cuth: no memory for the on-chip exchange; using sweep launches\n");
+            return Status::ok();
+        }
         E.res_cap = words;
         E.res_gcap = plan.groups;
         E.res_ready = false;
@@ -3057,26 +3073,27 @@ Status residual(Grid &g, double dt, const double *b, const double *T, double *r)
 }
 
 template <typename T>
-static Status precond_typed(Grid &g, Setup &su, Work<T> &w, const Shape &sh, const ChebConsts &cc,
+static Status precond_typed(Grid &g, Setup &su, Work<T> &w, Shape &sh, const ChebConsts &cc,
                             int pm, bool h16, const T *r, T *z) {
-    // the result lands in the buffer the sweep rotation ends in (fused pairs
-    // exactly where enqueue_precond uses them: FP32)
     Engine &E = g.eng;
     const bool h16e = h16 && g.per_cell;
-    const int zfin = precond_final(cc.k, pm, fuse_for<T>(sh, pm));
     Problem p;
     p.g = &g;
     p.su = &su;
     p.cc = cc;
     p.pm = pm;
     p.h16 = h16e;
+    p.inner = true;
+    std::vector<Problem *> ps{&p};
+    if (sh.res.nzc > 0) CUTH_TRY(res_prepare<T>(E, ps, sh, g.stream));
+    // the result lands in the buffer the sweep rotation ends in (fused pairs
+    // exactly where enqueue_precond uses them: FP32)
+    const int zfin = precond_final(cc.k, pm, fuse_for<T>(sh, pm));
     Work<T> &pw = Sel<T>::w(p);
     pw = w;
     pw.r = const_cast<T *>(r);
     T **zs[4] = {&pw.zA, &pw.zB, &pw.zC, &pw.zD};
     *zs[zfin] = z;
-    p.inner = true;
-    std::vector<Problem *> ps{&p};
     std::vector<int> which;
     const int nb = build_inner<T>(E, ps, sh, which);
     if (nb < 0) return Status::err(CUTH_E_DEVICE, "internal: preconditioner does not fit the engine");
@@ -3086,7 +3103,6 @@ static Status precond_typed(Grid &g, Setup &su, Work<T> &w, const Shape &sh, con
     CgState<T> *hs = Sel<T>::hs(E);
     std::memset(hs, 0, sizeof(CgState<T>));
     CUTH_HIP(hipMemcpyAsync(Sel<T>::ds(E), hs, sizeof(CgState<T>), hipMemcpyHostToDevice, g.stream));
-    if (sh.res.nzc > 0) CUTH_TRY(res_prepare<T>(E, ps, sh, g.stream));
     const int got = enqueue_precond<T>(E, 1, nb, g.per_cell, p.h16 ? CS_F16 : CS_OWN, pm, sh, cc.k,
                                        false, false, g.stream, nullptr);
     if (got != zfin) return Status::err(CUTH_E_DEVICE, "internal: preconditioner buffer mismatch");
@@ -3173,7 +3189,8 @@ Status precond_apply(Grid &g, double dt, int precision, int pm, double lmin, dou
     st = precond_typed<double>(g, *su, g.w64, sh64, cc, pm, false, (const double *)r, (double *)z);
     if (st.bad() || sh64.res.nzc == 0 || !g.eng.h_st64->gave_up) return st;
     res_failed(g.eng);
-    return precond_typed<double>(g, *su, g.w64, g.sh64, cc, pm, false, (const double *)r, (double *)z);
+    sh64.res = ResShape{};
+    return precond_typed<double>(g, *su, g.w64, sh64, cc, pm, false, (const double *)r, (double *)z);
 }
 
 // z = M^{-1} r as precond_typed runs it on chip (rs) or with single sweeps, but
