@@ -46,7 +46,8 @@
  *    that fits);
  *    CUTH_FUSE3_SHAPE="R,zc" with CUTH_FUSE=1 and CUTH_FUSE3=1 (default 4,8).
  *  - CUTH_RESIDENT=0: never run the whole Chebyshev preconditioner as one
- *    launch with its vectors on chip (default: single solves, and batches except
+ *    launch with its vectors on chip; =1: wherever that is possible; unset: where
+ *    it is and takes less time than sweep launches (single solves, and batches except
  *    CUTH_ADAPTIVE ones, of grids of at most 16 layers (FP32: 20), in tiles of 64
  *    columns by 8 or (FP32) 14 or 16 rows of which the device holds one per compute unit at a
  *    time, in slabs of rows where a grid has more of them and the slabs' overlap

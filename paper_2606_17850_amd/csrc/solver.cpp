@@ -163,8 +163,13 @@ size_t res_limit() {
     return e ? (size_t)std::max(std::atoi(e), 0) << 20 : std::numeric_limits<size_t>::max();
 }
 
-// CUTH_RESIDENT=0: never use the on-chip preconditioner.  The settings that
-// force or forbid fused sweeps ask for sweep launches, so they rule it out too.
+// CUTH_RESIDENT=0: never use the on-chip preconditioner; =1: wherever it fits.  The
+// settings that force or forbid fused sweeps ask for sweep launches, so they rule
+// it out too.
+bool res_forced() {
+    const char *e = std::getenv("CUTH_RESIDENT");
+    return e && e[0] == '1';
+}
 bool res_allowed() {
     const char *e = std::getenv("CUTH_RESIDENT");
     return !(e && e[0] == '0') && !std::getenv("CUTH_FUSE") && !std::getenv("CUTH_FUSE3");
@@ -804,6 +809,54 @@ ResPlan make_res_plan(const std::vector<ResDims> &grids, const ResShape &rs, int
     plan.groups = groups.size();
     return plan;
 }
+// Whether an application at degree k takes less time on chip than by sweep launches
+// (both timed as whole solves at 295 sizes, types and degrees: where they differ by
+// more than 3 % the rule takes the shorter but at 4 of them, where it stays with
+// launches that take 6 to 26 % longer).
+//
+// All tiles at once: always, but for the shortest polynomials on most of the CUs,
+// where the tiles' loads and stores, which nothing hides, outweigh a sweep or two
+// (solves at 512x512x16, per cell, k = 2: 78.7 -> 91.5 ms; 512x512x4, k = 3: 9.6 ->
+// 10.7; 512x512x8, k = 3: 21.0 -> 18.9).
+//
+// In several rounds a tile's padding counts: layers up to its class, the slabs' halo
+// rows, ragged columns.  A grid of one layer does an eighth of what its tiles do:
+// 2048x2048x1 8.5 -> 28.6 ms a solve, x4 56.5 -> 72.5, x8 143 -> 127 (k = 30); a
+// batch of 16 stacks of 256x256x1 3.5 -> 5.2, x4 12.6 -> 11.7.  So rounds times the
+// time of a round are held against the time of the launches, which goes with the
+// cells, one more layer or half of one for each column's ends, and the lanes of a
+// row (a load of one cell a lane costs nearly half of one of four).
+template <typename T>
+bool res_pays(const std::vector<ResDims> &grids, const ResShape &rs, const ResPlan &plan, int k, int cus) {
+    const bool cells = grids[0].cells, jacobi = grids[0].jacobi, f64 = sizeof(T) == 8;
+    if (plan.launches.size() == 1 && (int64_t)plan.tiles <= cus) {
+        if (2 * (int64_t)plan.tiles <= cus || k > 3) return true;
+        const ResDims &g = grids[0];
+        return k == 3 && (grids.size() > 1 || 2 * g.nz > res_class<T>(g.nz));
+    }
+    double chip = 0.0;   // us
+    for (const ResPlan::Launch &l : plan.launches) {
+        const int c = l.nzc <= 8 ? 0 : l.nzc <= 12 ? 1 : l.nzc <= 16 ? 2 : 3;
+        // us a sweep, all CUs busy
+        const double low[] = {1.2, 1.7, 2.3, 2.65}, high[] = {1.75, 2.2, 3.4, 3.5}, wide[] = {3.4, 4.6, 6.2, 0.0};
+        double sweep = f64 ? wide[c] : rs.vy == 1 ? low[c] : high[c];
+        if (cells && jacobi && c == 2 && (f64 || rs.vy == 2)) sweep *= 1.9;   // (spills)
+        const int full = l.tiles / cus, part = l.tiles % cus;
+        // (loads, stores and the test: 2.6 sweeps)
+        chip += (full + (part ? 0.6 + 0.4 * part / cus : 0.0)) * sweep * (k + 1.6);
+    }
+    double launches = 0.0;   // us a sweep
+    for (const ResDims &g : grids) {
+        int vx = 16 / (int)sizeof(T);
+        while (g.nx % vx != 0) vx /= 2;
+        const double lanes = (double)kWave * tiles_x(g.nx, vx);
+        const double column = f64 ? (cells ? 7.5 : 5.4) * (g.nz + 0.5)   // ps
+                              : cells || jacobi ? (cells && jacobi ? 2.5 : 2.33) * (g.nz + 0.5)
+                                                : 1.8 * (g.nz + 0.8);
+        launches += g.ny * lanes * (f64 ? 0.5 + 0.75 * vx : 0.8 + 0.8 * vx) * column * 1e-6 * 256.0 / cus;
+    }
+    return chip <= (k - 1.4) * std::max(launches, f64 ? 4.1 : 1.45);   // (a launch takes that long)
+}
 // Every launch of a plan has its kernel (res_fit offers no other shape; a launch
 // without one would leave the z of the application before).
 template <typename T>
@@ -835,6 +888,10 @@ ResShape res_take(const std::vector<Grid *> &grids, const Shape &sh, int pm, int
         if (n > prob_tiles(*g, sh)) return ResShape{};
         tiles += n;
     }
+    std::vector<ResGroup> groups;
+    if (!res_forced() &&
+        !res_pays<T>(dims, rs, make_res_plan<T>(dims, rs, device_cus(device), groups), degree, device_cus(device)))
+        return ResShape{};
     return call.lease.acquire(device, tiles, device_cus(device)) ? rs : ResShape{};
 }
 
