@@ -19,10 +19,14 @@ switched off; its average duration comes from HIP events the library records
 on its own stream around each back-to-back run of those launches.  Those
 events add gaps between launches, so they are recorded in separate solves:
 the solves whose wall time is reported run without them.
-roofline_blocked = the launch that carries the sweeps in the default solve
-(fused triples of sweeps where the tuner picks them), with its own bytes
+roofline_blocked = the launch that carries the sweeps where they run by
+launches (fused triples of sweeps where the tuner picks them), with its own bytes
 (28 B per unknown for three sweeps: z_{j+1} stays on chip) and the bytes of
-the three single sweeps it replaces.  traffic = HBM bytes per launch from
+the three single sweeps it replaces.  Both are timed in solves with kernel timing
+on, which run the sweeps by launches; the reported solves apply the whole
+preconditioner in one launch with its vectors on chip (k_cheb_res), which is not
+bound by HBM, so neither object describes their preconditioner, and value counts
+the few bytes such an application moves.  traffic = HBM bytes per launch from
 rocprofv3 FETCH_SIZE + WRITE_SIZE counters (profiles/), when they were taken on
 the current kernel source; else null.
 

@@ -61,7 +61,7 @@
  *    in rounding, and a handle that has seen two such keeps to them for its next 8
  *    calls (16 if it then gives up again, and so on up to 1024).
  *    CUTH_RESIDENT_MB=<n>: device memory in MiB that a handle's (or batch's)
- *    exchange between tiles may take, about 20 to 80 KiB a tile; above it, or where
+ *    exchange between tiles may take, 18 to 72 KiB a tile; above it, or where
  *    there is no memory for it, sweep launches.
  *    CUTH_RESIDENT_SPIN=<n>[@<m>]: polls its tiles wait for each other before
  *    the application is repeated with sweep launches (default 32768); with @<m>
@@ -381,9 +381,9 @@ cuth_status cuth_precond_apply(cuth_grid g, double dt, int32_t precision, int32_
  * cleared on every call.  The sweeps run on chip where cuth_precond_apply's do,
  * else one per launch (never fused).  Scratch needed: about N * 4 bytes (FP32,
  * CUTH_MIXED and CUTH_MIXED16) or N * 8 bytes (CUTH_FP64), plus a few KiB and
- * 384 bytes per stencil workgroup (and up to 42 KiB per on-chip tile; where that
- * does not fit besides, both calls run the sweeps by launches); a grid that needs
- * more returns
+ * 384 bytes per stencil workgroup (and 18 to 49 KiB per on-chip tile, FP64 36 to
+ * 72; where that does not fit besides, both calls run the sweeps by launches); a
+ * grid that needs more returns
  * CUTH_E_INVALID before any device work, with the sizes in cuth_last_error().
  * All calls on one GPU share its array: calls that overlap in time on one GPU
  * (other host threads, other streams) race and give undefined results.  Returns

@@ -16,8 +16,7 @@ namespace cuth {
 
 constexpr int kMaxLayers = 64;
 constexpr int kWave = 64;          // CDNA wavefront
-constexpr int kMaxBY = 8;          // rows (wavefronts) per workgroup
-constexpr int kMaxWaves = 16;      // wavefronts of any workgroup
+constexpr int kMaxBY = 8;          // rows (wavefronts) per workgroup, on-chip tiles included
 constexpr int kRedBlocks = 1024;   // workgroups of the 1-D (non-stencil) reduction kernels
 
 // Per-layer coefficients (uniform within a layer).

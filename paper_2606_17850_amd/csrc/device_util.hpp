@@ -180,7 +180,7 @@ __device__ __forceinline__ bool finite_val(T v) {
 template <typename T, int NV>
 __device__ __forceinline__ void block_partials(T (&v)[NV], unsigned maxmask, T *part, int nb,
                                                int slot) {
-    __shared__ T sh[NV][kMaxWaves];
+    __shared__ T sh[NV][kMaxBY];
     const int lane = threadIdx.x, w = threadIdx.y, nw = blockDim.y;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
@@ -204,7 +204,7 @@ __device__ __forceinline__ void block_partials(T (&v)[NV], unsigned maxmask, T *
 // of every workgroup obtains the same value.
 template <typename T>
 __device__ __forceinline__ T reduce_prev(const T *part, int np) {
-    __shared__ T sh[kMaxWaves];
+    __shared__ T sh[kMaxBY];
     // 16 independent loads in flight per lane (one L2 round trip per 1024
     // partials of a 64-lane workgroup), then a fixed-order combine
     constexpr int U = 16;

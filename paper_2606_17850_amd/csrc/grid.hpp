@@ -68,7 +68,7 @@ struct Shape {
 };
 
 // Launches of the on-chip preconditioner for a set of problems: one per layer
-// class (8, 12, 16), of `tiles` tiles in groups [g0, g0 + gn) by `width` workgroups,
+// class (8, 12, 16, FP32: 20), of `tiles` tiles in groups [g0, g0 + gn) by `width` workgroups,
 // its edge words from word0 and its tiles' epochs from tile0 on.
 struct ResPlan {
     struct Launch {

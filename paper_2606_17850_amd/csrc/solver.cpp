@@ -240,7 +240,14 @@ int64_t res_tiles(int nx, int ny, const ResShape &rs, int cus) {
 // not fit at once goes through the
 // device in groups of the largest tile, which does the most work per exchange
 // (2.8 us a sweep for 4.2 M unknowns on all CUs, where launches take 8 to 10),
-// as long as the slabs of a grid compute at most twice its own rows.
+// as long as the slabs of a grid compute at most twice its own rows and res_pays
+// finds it the shorter way.
+//
+// Layer counts end where a column's values fill the registers (256 a lane): FP32 20
+// layers (255 of them with two rows a lane, 234 to 256 with one), FP64 16.  A grid with
+// more, and a batch with one such grid, keeps to launches: the problems of a batch
+// advance in the same launches of a captured chunk, so they have one preconditioner
+// path and one tile (with 17 to 20 layers among thinner ones the 8-row one).
 //
 // FP64 tiles hold half the rows, exchange twice the words for each and, with the
 // Jacobi scale in registers, spill: slabs pay only for per-cell conductances
