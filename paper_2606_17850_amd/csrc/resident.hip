@@ -7,11 +7,12 @@
 // workgroup owns a tile of 64 x (VY NW) whole columns of the grid, a lane VY
 // columns, and z_j, z_{j-1}, r and the conductances stay in registers from the
 // first sweep to the last.  A sweep then costs its arithmetic (14.5 vector
-// instructions per unknown) and one exchange of the tile's edge values with the
+// instructions per unknown; 19 to 23 with all around it) and one exchange of the tile's edge values with the
 // four neighbouring tiles (about 1 us through memory, behind the arithmetic
 // where that is long enough).  Per sweep, launches as before -> here: 512x512x16
-// per cell 10.0 -> 2.9 us (256 tiles of 64 x 16 columns: the arithmetic of two
-// wavefronts per SIMD, which issue an instruction every 5.5 cycles each),
+// per cell 10.0 -> 2.9 us (256 tiles of 64 x 16 columns, two wavefronts per SIMD: a
+// wavefront issues a vector instruction every 12 cycles, 5.5 being the least, and
+// waits for edges, LDS and barriers 38 % of the time),
 // 256x256x10 4.0 -> 1.5 us, 64x64x8 3.6 -> 1.1 us (the exchange).
 //
 // Tiles.  64 x 8 columns where the CUs hold all such tiles at once, one each, else
