@@ -29,11 +29,11 @@ public:
         pool_->freed.notify_all();
     }
     // Waits for `width` of the device's `units` (false: a device out of range).
-    bool acquire(int device, int64_t width, int units) {
+    bool acquire(int device, int width, int units) {
         static Pool pools[kDevices];
         if (device < 0 || device >= kDevices || units <= 0) return false;
         Pool &p = pools[device];
-        const int need = (int)std::min<int64_t>((width + 7) / 8 * 8, units);
+        const int need = std::min((width + 7) / 8 * 8, units);
         std::unique_lock<std::mutex> lock(p.mu);
         const uint64_t ticket = p.arrived++;
         p.freed.wait(lock, [&] { return p.serving == ticket && p.used + need <= units; });

@@ -889,17 +889,15 @@ ResShape res_take(const std::vector<Grid *> &grids, const Shape &sh, int pm, int
     const ResShape rs = res_fit<T>(dims, device, degree);
     if (rs.nzc == 0) return rs;
     // (one partial sum per tile goes into the sweeps' workgroup slots)
-    int64_t tiles = 0;
-    for (const Grid *g : grids) {
-        const int64_t n = res_tiles(g->nx, g->ny, rs, device_cus(device));
-        if (n > prob_tiles(*g, sh)) return ResShape{};
-        tiles += n;
-    }
+    const int cus = device_cus(device);
+    for (const Grid *g : grids)
+        if (res_tiles(g->nx, g->ny, rs, cus) > prob_tiles(*g, sh)) return ResShape{};
     std::vector<ResGroup> groups;
-    if (!res_forced() &&
-        !res_pays<T>(dims, rs, make_res_plan<T>(dims, rs, device_cus(device), groups), degree, device_cus(device)))
-        return ResShape{};
-    return call.lease.acquire(device, tiles, device_cus(device)) ? rs : ResShape{};
+    const ResPlan plan = make_res_plan<T>(dims, rs, cus, groups);
+    if (!res_forced() && !res_pays<T>(dims, rs, plan, degree, cus)) return ResShape{};
+    int width = 0;
+    for (const ResPlan::Launch &l : plan.launches) width = std::max(width, l.width);
+    return call.lease.acquire(device, width, cus) ? rs : ResShape{};
 }
 
 // Tiles of the CG kernels for a grid whose preconditioner is on chip (a shape set
