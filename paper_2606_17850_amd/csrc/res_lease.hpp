@@ -30,7 +30,8 @@ public:
     }
     // Waits for `width` of the device's `units` (false: a device out of range).
     bool acquire(int device, int width, int units) {
-        static Pool pools[kDevices];
+        // (never destroyed: a thread may still wait here when the process ends)
+        static Pool *const pools = new Pool[kDevices];
         if (device < 0 || device >= kDevices || units <= 0) return false;
         Pool &p = pools[device];
         const int need = std::min((width + 7) / 8 * 8, units);

@@ -5,11 +5,24 @@
 #include <atomic>
 #include <chrono>
 #include <cstdio>
+#include <cstdlib>
 #include <random>
 #include <thread>
 #include <vector>
 
-int main() {
+int main(int argc, char **) {
+    if (argc > 1) {   // the process ends while a thread waits
+        auto *all = new cuth::ResLease;   // (held to the end)
+        (void)all->acquire(0, 256, 256);
+        std::thread([] {
+            cuth::ResLease more;
+            (void)more.acquire(0, 8, 256);
+        }).detach();
+        std::this_thread::sleep_for(std::chrono::milliseconds(200));
+        std::printf("ok\n");
+        std::fflush(stdout);
+        std::exit(0);
+    }
     constexpr int kUnits = 256, kThreads = 8, kTurns = 400;
     std::atomic<int> held{0}, wide{0}, together{0}, over{0}, refused{0};
     std::vector<std::thread> threads;
