@@ -53,9 +53,9 @@
  *    time, in slabs of rows where a grid has more of them and the slabs' overlap
  *    at most doubles the work (FP64: plain Chebyshev on per-cell conductances
  *    only); CUTH_FUSE or CUTH_FUSE3 set, or kernel timing on, asks for sweep
- *    launches).  Solves of several threads share the device's compute units: one
- *    that needs more than the others leave waits for them, in the order of arrival,
- *    so that results do not depend on other threads.  Other processes and other
+ *    launches).  Solves of several threads share the device's compute units: those
+ *    that want more than there are take turns of a few iterations, so that results do
+ *    not depend on other threads.  Other processes and other
  *    work on the device can hold compute units for longer than the bound below;
  *    the application is then repeated with sweep launches, whose results differ
  *    in rounding, and a handle that has seen two such keeps to them for its next 8

@@ -80,6 +80,8 @@ struct ResPlan {
     size_t words = 0, tiles = 0, groups = 0;
 };
 
+class ResLease;
+
 // Device descriptors, states and reduction partials for up to `cap` problems
 // solved together (a single solve uses a set of one).
 struct Engine {
@@ -106,6 +108,7 @@ struct Engine {
     int res_pause = 0;    // calls that keep to sweep launches before the next try
     int res_wait = 0;     // the last such number
     int res_applied = 0;  // applications enqueued since res_prepare
+    ResLease *res_lease = nullptr;   // of the call under way, where it runs on chip
     hipStream_t own = nullptr;                   // stream for graph capture
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
     // instantiated chunks of CG iterations, by launch configuration: a chunk's

@@ -727,7 +727,7 @@ void res_failed(Engine &E) {
 }
 
 // One call's use of the on-chip preconditioner: whether the engine may try it, and
-// the lease that goes with it.
+// its share of the compute units.
 struct ResCall {
     Engine &E;
     const int aborts;
@@ -739,9 +739,26 @@ struct ResCall {
             may = false;
         }
     }
-    ~ResCall() {   // (a call that ran on chip throughout)
-        if (lease.held() && E.res_aborts == aborts) E.res_aborts = E.res_wait = 0;
+    ~ResCall() {
+        E.res_lease = nullptr;
+        // (a call that ran on chip throughout)
+        if (lease.entered() && E.res_aborts == aborts) E.res_aborts = E.res_wait = 0;
     }
+};
+// The units for an inner solve's launches, from taking them to the next wait for the
+// stream.  By then the outer residual has been read back, so the stream waits for
+// nothing but them.
+struct ResTurn {
+    ResLease *lease;
+    ~ResTurn() { give(); }
+    void take() {
+        if (lease) lease->take();
+    }
+    void give() {
+        if (lease) lease->give();
+    }
+    // Iterations of `cnt` to run before the next wait.
+    int share(int cnt) const { return lease && lease->crowded() ? std::min(cnt, 2) : cnt; }
 };
 
 ResArgs res_args(const Engine &E, size_t q) {
@@ -879,7 +896,7 @@ Status res_built(const ResPlan &plan, ResShape rs, bool pc, bool jac) {
 inline size_t res_plan_words(const ResPlan &p) { return p.words + (p.tiles + 1) / 2; }
 
 // The on-chip shape for grids solved together on one device, where there is one
-// (the lease taken, for which this may wait); nzc 0 otherwise.
+// (the solve then shares the device's units by call.lease); nzc 0 otherwise.
 template <typename T>
 ResShape res_take(const std::vector<Grid *> &grids, const Shape &sh, int pm, int degree, ResCall &call) {
     if (!is_cheb(pm) || degree < 2 || !res_allowed() || !call.may) return ResShape{};
@@ -897,7 +914,9 @@ ResShape res_take(const std::vector<Grid *> &grids, const Shape &sh, int pm, int
     if (!res_forced() && !res_pays<T>(dims, rs, plan, degree, cus)) return ResShape{};
     int width = 0;
     for (const ResPlan::Launch &l : plan.launches) width = std::max(width, l.width);
-    return call.lease.acquire(device, width, cus) ? rs : ResShape{};
+    if (!call.lease.enter(device, width, cus)) return ResShape{};
+    call.E.res_lease = &call.lease;
+    return rs;
 }
 
 // Tiles of the CG kernels for a grid whose preconditioner is on chip (a shape set
@@ -1169,6 +1188,8 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, in
         p.stop = 0;
     }
     CUTH_HIP(hipMemcpyAsync(Sel<T>::ds(E), hs, sizeof(CgState<T>) * nprob, hipMemcpyHostToDevice, s));
+    ResTurn turn{sh.res.nzc > 0 ? E.res_lease : nullptr};
+    turn.take();
     int zfin = enqueue_precond<T>(E, nprob, nb, pc, cs, pm, sh, k, false, red, s, prof);
     bool graph = use_graph && period % 2 == 0;
     // instantiated chunk of `len` iterations (len even: the arguments repeat
@@ -1220,23 +1241,32 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, in
         // at or after the predicted stop, never one iteration before it, where
         // the stagnation test could fire on the FP32 plateau)
         if (pred > it && pred - it < cnt) cnt = graph ? (pred - it + 1) & ~1 : pred - it;
-        if (graph) {
-            hipGraphExec_t ex = exec;
-            if (cnt != period) {
-                if (!exec2) CUTH_TRY(chunk_graph(2, exec2));
-                ex = exec2;
-            }
-            for (int q = 0; q < (cnt == period ? 1 : cnt / 2); ++q) {
-                const hipError_t le = hipGraphLaunch(ex, s);
-                if (le != hipSuccess) {
-                    result = Status::err(CUTH_E_DEVICE, std::string("hipGraphLaunch: ") + hipGetErrorString(le));
-                    break;
+        for (int ran = 0; ran < cnt && !result.bad();) {
+            turn.take();
+            const int n = turn.share(cnt - ran);
+            if (graph) {
+                hipGraphExec_t ex = exec;
+                if (n != period) {
+                    if (!exec2) CUTH_TRY(chunk_graph(2, exec2));
+                    ex = exec2;
                 }
+                for (int q = 0; q < (n == period ? 1 : n / 2); ++q) {
+                    const hipError_t le = hipGraphLaunch(ex, s);
+                    if (le != hipSuccess) {
+                        result = Status::err(CUTH_E_DEVICE, std::string("hipGraphLaunch: ") + hipGetErrorString(le));
+                        break;
+                    }
+                }
+            } else {
+                enqueue_iterations<T>(E, nprob, nb, pc, cs, pm, sh, k, it + ran, n, zfin, red, s, prof);
             }
-            if (result.bad()) break;
-        } else {
-            enqueue_iterations<T>(E, nprob, nb, pc, cs, pm, sh, k, it, cnt, zfin, red, s, prof);
+            ran += n;
+            if (ran < cnt) {
+                CUTH_TRY(sync_stream(s));
+                turn.give();
+            }
         }
+        if (result.bad()) break;
         it += cnt;
         launch_check_b<T>(Sel<T>::d(E), nprob, nb, pc, cs, sh.vx, sh.by, eslot<T>(E, P_CHK), s);
         ++nchecks;
@@ -1244,12 +1274,14 @@ Status inner_solve(Engine &E, std::vector<Problem *> &ps, const Shape &sh_in, in
         CUTH_HIP(hipMemcpyAsync(E.h_part, eslot<T>(E, P_CHK), sizeof(T) * 2 * (size_t)nb,
                                 hipMemcpyDeviceToHost, s));
         CUTH_TRY(sync_stream(s));
+        turn.give();
         if (sh.res.nzc > 0 && nprob == 1 && hs[0].gave_up) {
             // (a single problem) the tiles of an on-chip application waited in
             // vain for each other: x and r are those after st.iter iterations,
             // z is repeated from r with sweep launches and the iteration goes on
             res_failed(E);
             sh.res = ResShape{};
+            turn.lease = nullptr;
             graph = false;
             hs[0].done = hs[0].gave_up = 0;
             CUTH_HIP(hipMemcpyAsync(Sel<T>::ds(E), hs, sizeof(CgState<T>), hipMemcpyHostToDevice, s));
@@ -1657,11 +1689,21 @@ Status inner_solve_staged(Engine &E, std::vector<Problem *> &ps, const Shape &sh
         launch_promote_dot<double>(d, nprob, nb, sh64.vx, sh64.by, eslot<double>(E, P_CHEB), s);
         if (red) launch_reduce_b<double>(d, nprob, eslot<double>(E, P_CHEB), red_rz<double>(E), s);
     };
+    ResTurn turn{sh32.res.nzc > 0 ? E.res_lease : nullptr};
+    turn.take();
     precond();
     int it = 0, nchecks = 0, on_chip = 0, repeated = 0;   // (as in inner_solve)
     while (it < maxit) {
         const int cnt = std::min(period, maxit - it);
-        for (int q = 0; q < cnt; ++q) {
+        for (int q = 0, until = 0; q < cnt; ++q) {
+            if (q == until) {
+                if (q > 0) {
+                    CUTH_TRY(sync_stream(s));
+                    turn.give();
+                }
+                turn.take();
+                until = q + turn.share(cnt - q);
+            }
             const int par = (it + q) & 1;
             launch_dir_b<double>(d, nprob, nb, pc, early ? CS_F32 : CS_OWN, sh64.vx, sh64.by, par, 0,
                                  red ? red_rz<double>(E) : eslot<double>(E, P_CHEB), red,
@@ -1681,10 +1723,12 @@ Status inner_solve_staged(Engine &E, std::vector<Problem *> &ps, const Shape &sh
         CUTH_HIP(hipMemcpyAsync(E.h_part, eslot<double>(E, P_CHK), sizeof(double) * 2 * (size_t)nb,
                                 hipMemcpyDeviceToHost, s));
         CUTH_TRY(sync_stream(s));
+        turn.give();
         if (sh32.res.nzc > 0 && hs[0].done == kResAbort) {
             // as in inner_solve: z again by sweep launches, then on
             res_failed(E);
             sh32.res = ResShape{};
+            turn.lease = nullptr;
             zfin32 = precond_final(k, pm, fuse_for<float>(sh32, pm));
             h64[0].z_lo = zfin32 == 0 ? ps[which[0]]->w32.zA : ps[which[0]]->w32.zB;
             hs[0].done = 0;
@@ -2493,7 +2537,6 @@ Status solve_system(Grid &g, double dt, const double *P, const double *Tn, const
     Status st;
     cuth_options o = o_in;
     if (o.cheb_degree > g.eng.kcap) return Status::err(CUTH_E_INVALID, "cheb_degree above 256");
-    CUTH_TRY(sync_stream(g.stream));   // (before a lease is taken)
     CUTH_HIP(hipEventRecord(g.ev0, g.stream));
     Setup *su = get_setup(g, dt, st);
     if (!su) return st;
@@ -2882,7 +2925,6 @@ Status solve_batch(int nsys, Grid *const *grids, int nrhs, const double *const *
     const bool mixed = o.precision == CUTH_MIXED || o.precision == CUTH_MIXED16 || o.precision == CUTH_FP32;
     const bool staged = o.precision == CUTH_ADAPTIVE;
     const hipStream_t user = grids[0]->stream;
-    CUTH_TRY(sync_stream(user));   // (before a lease is taken)
     // per-system setup (Lanczos bounds cached in each grid)
     std::vector<Setup *> sus(nsys);
     for (int s = 0; s < nsys; ++s) {
@@ -3225,7 +3267,7 @@ Status precond_apply(Grid &g, double dt, int precision, int pm, double lmin, dou
                      int degree, const void *r, void *z) {
     Status st;
     if (degree > g.eng.kcap) return Status::err(CUTH_E_INVALID, "degree above 256");
-    CUTH_TRY(sync_stream(g.stream));   // (before a lease is taken)
+    CUTH_TRY(sync_stream(g.stream));   // (before units are taken: see ResLease)
     Setup *su = get_setup(g, dt, st);
     if (!su) return st;
     // Jacobi and none are single passes; their degree is 1 (the constants are unused)
@@ -3236,6 +3278,7 @@ Status precond_apply(Grid &g, double dt, int precision, int pm, double lmin, dou
         if (sh32.fr > 0) CUTH_TRY(alloc_work(g.w32, g.N, true));
         ResCall call(g.eng);
         sh32.res = precond_res<float>(g, g.sh32, std::max(cc.k, 1), res_take<float>({&g}, sh32, pm, cc.k, call));
+        if (sh32.res.nzc > 0) call.lease.take();
         st = precond_typed<float>(g, *su, g.w32, sh32, cc, pm, precision == CUTH_MIXED16,
                                   (const float *)r, (float *)z);
         if (st.bad() || sh32.res.nzc == 0 || !g.eng.h_st32->gave_up) return st;
@@ -3248,6 +3291,7 @@ Status precond_apply(Grid &g, double dt, int precision, int pm, double lmin, dou
     Shape sh64 = g.sh64;
     ResCall call(g.eng);
     sh64.res = precond_res<double>(g, g.sh64, std::max(cc.k, 1), res_take<double>({&g}, sh64, pm, cc.k, call));
+    if (sh64.res.nzc > 0) call.lease.take();
     st = precond_typed<double>(g, *su, g.w64, sh64, cc, pm, false, (const double *)r, (double *)z);
     if (st.bad() || sh64.res.nzc == 0 || !g.eng.h_st64->gave_up) return st;
     res_failed(g.eng);
@@ -3380,12 +3424,13 @@ static Status precond_noalloc_typed(Grid &g, double dt, const ChebConsts &cc, in
 Status precond_apply_noalloc(Grid &g, double dt, int precision, int pm, double lmin, double lmax,
                              int degree, const void *r, void *z) {
     const ChebConsts cc = make_cheb(lmin, lmax, is_cheb(pm) ? degree : 1);
-    CUTH_TRY(sync_stream(g.stream));   // (before a lease is taken)
+    CUTH_TRY(sync_stream(g.stream));   // (before units are taken: see ResLease)
     bool aborted = false;
     if (precision != CUTH_FP64) {
         const bool h16 = precision == CUTH_MIXED16;
         ResCall call(g.eng);
         const ResShape rs = res_take<float>({&g}, g.sh32, pm, cc.k, call);
+        if (rs.nzc > 0) call.lease.take();
         Status st = precond_noalloc_typed<float>(g, dt, cc, pm, h16, (const float *)r, (float *)z, rs, aborted);
         if (st.bad() || !aborted) return st;
         res_failed(g.eng);
@@ -3393,6 +3438,7 @@ Status precond_apply_noalloc(Grid &g, double dt, int precision, int pm, double l
     }
     ResCall call(g.eng);
     const ResShape rs = res_take<double>({&g}, g.sh64, pm, cc.k, call);
+    if (rs.nzc > 0) call.lease.take();
     const Status st = precond_noalloc_typed<double>(g, dt, cc, pm, false, (const double *)r, (double *)z, rs, aborted);
     if (st.bad() || !aborted) return st;
     res_failed(g.eng);
